@@ -306,6 +306,7 @@ template <typename T> void launch_nbr_lists(Ctx &c, bool filter);
 template <typename T> void launch_pre_records(Ctx &c);
 template <typename T> void launch_wall(Ctx &c, int mode, bool cand_lists = false);
 template <typename T> void launch_pass(Ctx &c, int mode, bool cand_lists = false);
+template <typename T, int DIM> void launch_pass_dim(Ctx &c, int mode, bool cand_lists);  // dtsph_pair.hip
 void launch_finalize(Ctx &c, bool publish);
 // iteration next-1's residual reduction together with iteration next's wall pass
 template <typename T> void launch_finalize_wall(Ctx &c, bool publish, int next);

@@ -1,9 +1,7 @@
-// Pair-pass launches of the frozen-particle dual-time EDAC SPH step, and the
-// per-particle kernels around them (records, corrector, particle shifting,
-// state transfer). The pair pass, wall pass and residual reduction themselves
-// are in dtsph_pass_dev.h.
-#include <hip/hip_ext.h>
-
+// The per-particle kernels around the pair pass of the frozen-particle dual-time
+// EDAC SPH step (records, corrector, particle shifting, state transfer) and the
+// launches of the wall pass and residual reduction, whose device code is in
+// dtsph_pass_dev.h. The pair pass itself is launched from dtsph_pair.hip.
 #include <type_traits>
 
 #include "dtsph_pass_dev.h"
@@ -407,97 +405,15 @@ __global__ void k_get_state(StateArgs<T> A)
 inline int grid_for(int n, int b = 256) { return n > 0 ? ceil_div(n, b) : 1; }
 
 
-// A timed pair pass goes through hipExtLaunchKernelGGL, whose events take the
-// kernel's own start and end timestamps (no queue gaps in the interval).
-// Pseudo-iterations of a context with steady sims take the variant with the
-// convective sum (zero coefficient for the time-accurate sims).
-template <typename T, int DIM, bool WALLS, bool AV, bool SEPDEN, int LPP, bool CONV, int CACHE, bool MOVE = false>
-void launch_pseudo(Ctx &c, const PassArgs<T> &a, dim3 grid)
-{
-    if (c.ext_start)
-        hipExtLaunchKernelGGL((k_pass<T, DIM, WALLS, AV, SEPDEN, MODE_PSEUDO, LPP, CONV, CACHE, MOVE>), grid,
-                              dim3(c.block), 0, c.stream, c.ext_start, c.ext_stop, 0, a);
-    else
-        DTSPH_LAUNCH(c, (k_pass<T, DIM, WALLS, AV, SEPDEN, MODE_PSEUDO, LPP, CONV, CACHE, MOVE>), grid,
-                     dim3(c.block), 0, c.stream, a);
-}
-
-// Cached pair coefficients hold one regulariser: contexts with separate EDAC
-// or artificial-viscosity regularisers always recompute.
-template <typename T, int DIM, bool WALLS, bool AV, bool SEPDEN, int LPP, bool CONV>
-void dispatch_pseudo(Ctx &c, const PassArgs<T> &a, dim3 grid)
-{
-    if (SEPDEN || c.cache_phase == 0) launch_pseudo<T, DIM, WALLS, AV, SEPDEN, LPP, CONV, 0>(c, a, grid);
-    else if (c.cache_phase == 1) launch_pseudo<T, DIM, WALLS, AV, false, LPP, CONV, 1>(c, a, grid);
-    else launch_pseudo<T, DIM, WALLS, AV, false, LPP, CONV, 2>(c, a, grid);
-}
-
-template <typename T, int DIM, bool WALLS, bool AV, bool SEPDEN, int LPP>
-void dispatch_mode(Ctx &c, int mode, const PassArgs<T> &a, dim3 grid)
-{
-    if (mode == MODE_PRE)
-        DTSPH_LAUNCH(c, (k_pass<T, DIM, WALLS, AV, SEPDEN, MODE_PRE, LPP, false>), grid, dim3(c.block), 0, c.stream,
-                     a);
-    else if (c.any_move)  // moving particles: advective sums, no coefficient cache
-        launch_pseudo<T, DIM, WALLS, AV, SEPDEN, LPP, true, 0, true>(c, a, grid);
-    else if (c.any_steady)
-        dispatch_pseudo<T, DIM, WALLS, AV, SEPDEN, LPP, true>(c, a, grid);
-    else
-        dispatch_pseudo<T, DIM, WALLS, AV, SEPDEN, LPP, false>(c, a, grid);
-}
-
-template <typename T, int DIM, bool WALLS, bool AV, bool SEPDEN>
-void dispatch_lpp(Ctx &c, int mode, const PassArgs<T> &a, dim3 grid)
-{
-    switch (c.lpp) {
-    case 1: dispatch_mode<T, DIM, WALLS, AV, SEPDEN, 1>(c, mode, a, grid); break;
-    case 2: dispatch_mode<T, DIM, WALLS, AV, SEPDEN, 2>(c, mode, a, grid); break;
-    case 4: dispatch_mode<T, DIM, WALLS, AV, SEPDEN, 4>(c, mode, a, grid); break;
-    default: dispatch_mode<T, DIM, WALLS, AV, SEPDEN, 8>(c, mode, a, grid); break;
-    }
-}
-
-template <typename T, int DIM, bool WALLS, bool AV>
-void dispatch_sep(Ctx &c, int mode, const PassArgs<T> &a, dim3 grid)
-{
-    if (c.sep_den) dispatch_lpp<T, DIM, WALLS, AV, true>(c, mode, a, grid);
-    else dispatch_lpp<T, DIM, WALLS, AV, false>(c, mode, a, grid);
-}
-
-template <typename T, int DIM, bool WALLS>
-void dispatch_av(Ctx &c, int mode, const PassArgs<T> &a, dim3 grid)
-{
-    if (c.any_av) dispatch_sep<T, DIM, WALLS, true>(c, mode, a, grid);
-    else dispatch_sep<T, DIM, WALLS, false>(c, mode, a, grid);
-}
-
-template <typename T, int DIM>
-void dispatch_walls(Ctx &c, int mode, const PassArgs<T> &a, dim3 grid)
-{
-    if (c.any_walls) dispatch_av<T, DIM, true>(c, mode, a, grid);
-    else dispatch_av<T, DIM, false>(c, mode, a, grid);
-}
-
 }  // namespace
 
+// The pair pass of the context's dimension (its kernels: dtsph_pair.hip).
 template <typename T>
 void launch_pass(Ctx &c, int mode, bool cand_lists)
 {
-    PassArgs<T> a = pass_args<T>(c, mode, cand_lists);
-    if (a.n_tiles == 0) return;
-    const int grid = c.xcd_remap ? 8 * ((a.n_tiles + 7) / 8) : a.n_tiles;
-    const int t0 = mode == MODE_PSEUDO ? timer_slot(c, 0) : -1;
-    if (t0 >= 0) {
-        c.ext_start = c.ev_pool[t0];
-        c.ext_stop = c.ev_pool[t0 + 1];
-    }
-    if (c.max_dim == 2) dispatch_walls<T, 2>(c, mode, a, dim3(grid));
-    else dispatch_walls<T, 3>(c, mode, a, dim3(grid));
-    c.ext_start = c.ext_stop = nullptr;
-    DTSPH_HIP_CHECK(hipGetLastError());
-    timer_book(c, t0, 0);
+    if (c.max_dim == 2) launch_pass_dim<T, 2>(c, mode, cand_lists);
+    else launch_pass_dim<T, 3>(c, mode, cand_lists);
 }
-
 
 template <typename T>
 void launch_wall(Ctx &c, int mode, bool cand_lists)
