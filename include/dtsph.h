@@ -380,7 +380,9 @@ int dtsph_neighbor_list(dtsph_ctx *ctx, int32_t sim, int64_t *offsets, int32_t *
                                   in {1, 2, 3} (default 2); the search visits
                                   +-value cells per axis                      */
 #define DTSPH_OPT_NBR_LANES 9  /* lanes per particle of the neighbour-list
-                                  build: 1, 2, 4, 8 (0: automatic)           */
+                                  build: 1, 2, 4, 8 (0: automatic, which may
+                                  also take one wavefront per cell; the lists
+                                  and their order are the same)              */
 #define DTSPH_OPT_GRAPHS 10    /* 1: dtsph_step records the segment from the
                                   rate pass to the first chunk of pseudo-
                                   iterations as a HIP graph (one per launch
@@ -471,8 +473,9 @@ int dtsph_set_option(dtsph_ctx *ctx, int32_t option, int64_t value);
 
 /* Autotuner of the launch shapes. Between steps only (EINVAL in the loop).
  * Builds the cell lists if needed, picks the cell subdivision m in {1, 2, 3}
- * together with the neighbour kernel (lanes per particle 1, 2, 4, 8, or the
- * staged-tile kernel where it applies) by timing full builds of every pair
+ * together with the neighbour kernel (lanes per particle 1, 2, 4, 8, one
+ * wavefront per cell, or the staged-tile kernel where it applies) by timing
+ * full builds of every pair
  * (they only reorder the state), then times
  * the rate pass of the predictor (it writes only scratch between steps, so the state is unchanged)
  * for every lanes-per-particle in {1, 2, 4, 8} and workgroup size in {64, 128,
@@ -492,7 +495,8 @@ typedef struct dtsph_tune_report {
     int32_t n_entries, reserved;
     dtsph_tune_entry entries[12];
     int32_t nbr_lanes, filter_lanes; /* lanes per particle of the neighbour-list
-                                        build and of the candidate filter */
+                                        build (64: one wavefront per cell) and
+                                        of the candidate filter */
     double nbr_us, filter_us;
     int32_t cell_div;                /* cell subdivision and its full-build time */
     int32_t nbr_tiles;               /* 1: the staged-tile neighbour kernel */

@@ -252,6 +252,11 @@ void set_grid(SimDev &S, int m)
             S.cs[a] = S.inv_cs[a] = 1.0;
         }
     }
+    // the shift of a whole run of cells is exact when every periodic axis has at
+    // least 2m+3 cells (then a block's cells lie within half a period of its
+    // centre, by a margin of half a cell) and positions lie in [lo, hi)
+    S.general = 0;
+    for (int a = 0; a < S.dim; ++a) S.general |= S.periodic[a] && S.ncell[a] < 2 * m + 3;
     // strips of the staged neighbour kernel (2D): about 256 particles at the
     // lattice density, three times wider than tall (a strip row is one run of
     // consecutive keys)
@@ -327,6 +332,8 @@ void setup_keys(Ctx &c, int m)
     if (C > c.C_max) throw ApiError(DTSPH_EINVAL, "cell grid exceeds the key tables sized at creation");
     c.C = (int)C;
     c.cell_div = m;
+    c.grid_fast = c.grid_general = false;
+    for (const SimDev &S : c.sims_h) (S.general ? c.grid_general : c.grid_fast) = true;
     setup_strips(c);
 }
 
@@ -1725,8 +1732,9 @@ int dtsph_autotune(dtsph_ctx *ctx, int32_t repeats, dtsph_tune_report *out)
             for (int m = 1; m <= 3; ++m) {
                 setup_keys(c, m);
                 DTSPH_HIP_CHECK(hipMemcpy(c.sims, c.sims_h.data(), sizeof(SimDev) * c.n_sims, hipMemcpyHostToDevice));
-                // g = 0: the staged-tile kernel (where it applies), else lanes per particle
-                for (int g = 0; g <= 8; g = g ? 2 * g : 1) {
+                // g = 0: the staged-tile kernel (where it applies), 64: a wavefront per
+                // cell, else lanes per particle
+                for (int g : {0, 1, 2, 4, 8, 64}) {
                     if (g == 0 && c.n_strips == 0) continue;
                     c.nbr_tiles = g == 0 ? 1 : 0;
                     if (g > 0) c.g_nbr = g;

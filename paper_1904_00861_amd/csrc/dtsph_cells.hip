@@ -6,7 +6,7 @@
 //          -> k_scatter (provisional slot: cell start + arrival order)
 //          -> k_rank_gather (final slot: cell start + rank of the caller index
 //             among the cell's particles; every state array moved there)
-//          -> k_nbr (exact neighbour lists, candidate lists of radius kappa h +
+//          -> k_nbr / k_nbr_cell (exact neighbour lists, candidate lists of radius kappa h +
 //             skin, position records, pair counts).
 // Between builds, k_filter re-derives the exact lists from the candidate lists
 // at new positions, valid while no particle has moved more than skin/2 since
@@ -15,6 +15,7 @@
 // cell id): keys are dense and each cell holds a handful of particles, so one
 // histogram + scan + scatter moves the data once instead of once per 8-bit digit.
 #include <algorithm>
+#include <type_traits>
 
 #include "dtsph_internal.h"
 
@@ -690,74 +691,68 @@ __device__ __forceinline__ void scan_block(const NbrArgs<T> &A, const SimDev &S,
     ccw = cur.ctotal - ccf;
 }
 
-template <typename T, int DIM, int G>
-__global__ void __launch_bounds__(kThreads) k_nbr(NbrArgs<T> A)
+// GENERAL: the sims whose per-run shifts are not exact (SimDev::general); the
+// other launch takes the rest.
+template <typename T, int DIM, int G, bool GENERAL>
+__global__ void __launch_bounds__(kThreads) k_nbr(NbrArgs<T> A, const SimDev *__restrict__ sims)
 {
     using Q = typename XR<DIM>::type;
     const Group<G> grp;
     const int i = (blockIdx.x * blockDim.x + threadIdx.x) / G;
     if (i >= A.N) return;  // whole groups leave together
-    const int s = A.simid[i];
     const bool fluid = i < A.Nf;
-    const SimDev &S = A.sims[s];
     const Q me = ((const Q *)A.xr)[i];
-    const Probe<DIM> P = make_probe<DIM>(S, me.x, me.y, XR<DIM>::z(me));
-    if (grp.sub == 0) {
-        const double pos3[3] = {P.xi, P.yi, P.zi};
-        write_pos_record<T>(S, A.prec, i, pos3);
-    }
-    const int nx = S.ncell[0], ny = S.ncell[1], nz = DIM == 3 ? S.ncell[2] : 1;
-    const int cx = cell_coord(P.xi, S.lo[0], S.inv_cs[0], nx);
-    const int cy = cell_coord(P.yi, S.lo[1], S.inv_cs[1], ny);
-    const int cz = DIM == 3 ? cell_coord(P.zi, S.lo[2], S.inv_cs[2], nz) : 0;
-    // per-run shifts are exact when every periodic axis has at least 2m+3 cells
-    // (then a block's cells lie within half a period of its centre, by a margin
-    // of half a cell) and positions lie in [lo, hi)
-    const int m3 = 2 * S.cell_div + 3;
-    const bool general = (P.px && nx < m3) || (P.py && ny < m3) || (DIM == 3 && P.pz && nz < m3);
-    ListCursor cur;
-    int cf, cw, ccf, ccw;
-    if (general) scan_block<T, DIM, G, true>(A, S, i, P, cx, cy, cz, fluid, cf, cw, ccf, ccw, cur, grp);
-    else scan_block<T, DIM, G, false>(A, S, i, P, cx, cy, cz, fluid, cf, cw, ccf, ccw, cur, grp);
-    const int cap = A.cap, capc = A.capc;
-    if (cur.total > cap || cur.ctotal > capc) {
+    for_each_sim(A.simid[i], sims, [&](const SimDev &S) {
+        if ((S.general != 0) != GENERAL) return;
+        const Probe<DIM> P = make_probe<DIM>(S, me.x, me.y, XR<DIM>::z(me));
         if (grp.sub == 0) {
-            atomicOr(&A.flags[F_NBR_OVERFLOW], 1);
-            atomicMax(&A.flags[F_NBR_NEEDED], cur.total > cur.ctotal ? cur.total : cur.ctotal);
+            const double pos3[3] = {P.xi, P.yi, P.zi};
+            write_pos_record<T, DIM>(S, A.prec, i, pos3);
         }
-        cf = cf < cap ? cf : cap;
-        cw = cap - cf < cw ? cap - cf : cw;
-        ccf = ccf < capc ? ccf : capc;
-        ccw = capc - ccf < ccw ? capc - ccf : ccw;
-    }
-    if (grp.sub == 0) {
-        A.cnt[i] = (uint32_t)cf | ((uint32_t)cw << 16);
-        A.ccnt[i] = (uint32_t)ccf | ((uint32_t)ccw << 16);
-    }
+        const int cx = cell_coord(P.xi, S.lo[0], S.inv_cs[0], S.ncell[0]);
+        const int cy = cell_coord(P.yi, S.lo[1], S.inv_cs[1], S.ncell[1]);
+        const int cz = DIM == 3 ? cell_coord(P.zi, S.lo[2], S.inv_cs[2], S.ncell[2]) : 0;
+        ListCursor cur;
+        int cf, cw, ccf, ccw;
+        scan_block<T, DIM, G, GENERAL>(A, S, i, P, cx, cy, cz, fluid, cf, cw, ccf, ccw, cur, grp);
+        const int cap = A.cap, capc = A.capc;
+        if (cur.total > cap || cur.ctotal > capc) {
+            if (grp.sub == 0) {
+                atomicOr(&A.flags[F_NBR_OVERFLOW], 1);
+                atomicMax(&A.flags[F_NBR_NEEDED], cur.total > cur.ctotal ? cur.total : cur.ctotal);
+            }
+            cf = cf < cap ? cf : cap;
+            cw = cap - cf < cw ? cap - cf : cw;
+            ccf = ccf < capc ? ccf : capc;
+            ccw = capc - ccf < ccw ? capc - ccf : ccw;
+        }
+        if (grp.sub == 0) {
+            A.cnt[i] = (uint32_t)cf | ((uint32_t)cw << 16);
+            A.ccnt[i] = (uint32_t)ccf | ((uint32_t)ccw << 16);
+        }
+    });
 }
 
 // Exact lists at the current positions from the candidate lists of the last
 // build (same predicate, same order), plus new position records.
 template <typename T, int DIM, int G>
-__global__ void __launch_bounds__(kThreads) k_filter(NbrArgs<T> A)
+__global__ void __launch_bounds__(kThreads) k_filter(NbrArgs<T> A, const SimDev *__restrict__ sims)
 {
     using Q = typename XR<DIM>::type;
     const Group<G> grp;
     const int i = (blockIdx.x * blockDim.x + threadIdx.x) / G;
-    const bool active = i < A.N;
+    if (i >= A.N) return;  // whole groups leave together
     const int N = A.N;
-    const int s = active ? A.simid[i] : -1;
-    int cf = 0, cw = 0;
-    if (active) {
-        const SimDev &S = A.sims[s];
-        const Q *__restrict__ xr = (const Q *)A.xr;
-        const Q me = xr[i];
+    const Q *__restrict__ xr = (const Q *)A.xr;
+    const Q me = xr[i];
+    for_each_sim(A.simid[i], sims, [&](const SimDev &S) {
+        int cf = 0, cw = 0;
         const Probe<DIM> P = make_probe<DIM>(S, me.x, me.y, XR<DIM>::z(me));
         const int *__restrict__ cand = A.cand + i;
         int *__restrict__ nbr = A.nbr + i;
         if (grp.sub == 0) {
             const double pos3[3] = {P.xi, P.yi, P.zi};
-            write_pos_record<T>(S, A.prec, i, pos3);
+            write_pos_record<T, DIM>(S, A.prec, i, pos3);
         }
         const uint32_t cc = A.ccnt[i];
         const int ncf = (int)(cc & 0xffffu), nct = ncf + (int)(cc >> 16);
@@ -785,6 +780,231 @@ __global__ void __launch_bounds__(kThreads) k_filter(NbrArgs<T> A)
         }
         cw = total - cf;
         if (grp.sub == 0) A.cnt[i] = (uint32_t)cf | ((uint32_t)cw << 16);
+    });
+}
+
+// ---- one wavefront per cell ------------------------------------------------------
+// The particles of a cell share their candidates: the particles of the rows of cells
+// around it. A wavefront loads them 64 at a time, one per lane, and tests them against
+// the cell's particles one after the other (positions in scalar registers); the ballot
+// of a test is the hit mask of 64 consecutive candidates, so a lane's place in the list is
+// a count of the bits below it and the list keeps the sequential scan order. Hits are
+// collected in LDS and stored as rows of neighbouring particles. Against one lane group per
+// particle (k_nbr) a candidate's position is loaded once per cell, not once per particle,
+// and no lane waits for another's longer row; the tests are not trimmed to each particle's
+// own rows, which costs 2D (68 tests per particle for 45) what 3D gains, and there are
+// as many wavefronts as cells, which hides latency where particles are few (launch_grouped).
+constexpr int kCellBatch = 8;   // particles of the cell taken at a time
+constexpr int kCellRows = 128;  // list entries held per particle before they are stored
+constexpr int kCellPitch = kCellRows + 8;  // words: the 8 x 8 reads of a store take 64 banks
+
+// Inclusive prefix sum over the wavefront's 64 lanes (all active).
+__device__ inline int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+__device__ inline int sim_of_key(const SimDev *__restrict__ sims, int n_sims, int key)
+{
+    int a = 0, b = n_sims - 1;  // the last sim whose keys start at or below key
+    while (a < b) {
+        const int m = (a + b + 1) >> 1;
+        if (sims[m].key_base <= key) a = m;
+        else b = m - 1;
+    }
+    return a;
+}
+
+template <typename T, int DIM>
+__global__ void __launch_bounds__(kThreads)
+k_nbr_cell(NbrArgs<T> A, const SimDev *__restrict__ sims, const uint32_t *__restrict__ cstart,
+           const typename XR<DIM>::type *__restrict__ xr, int n_sims, int n_blocks)
+{
+    using Q = typename XR<DIM>::type;
+    using Cand = std::integral_constant<int, 0>;
+    using Exact = std::integral_constant<int, 1>;
+    __shared__ int lds[kThreads / 64][2][kCellBatch][kCellPitch];  // per wavefront: candidate, exact lists
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // consecutive cells on one XCD: they share most of their candidates (fluid cells
+    // first, then wall cells, each dealt to all XCDs)
+    int blk = (int)blockIdx.x;
+    const bool fluid = blk < n_blocks;
+    if (!fluid) blk -= n_blocks;
+    blk = (blk & 7) * (n_blocks >> 3) + (blk >> 3);  // n_blocks: a multiple of 8
+    int key = blk * (kThreads / 64) + wave;
+    if (key >= A.C) return;
+    if (!fluid) key += A.C;
+    const int i0 = (int)cstart[key], i1 = (int)cstart[key + 1];
+    if (i0 >= i1) return;
+    const SimDev &S = sims[sim_of_key(sims, n_sims, fluid ? key : key - A.C)];
+    if (S.general) return;  // k_nbr takes these sims
+    const int N = A.N, md = S.cell_div, nx = S.ncell[0], ny = S.ncell[1], nz = DIM == 3 ? S.ncell[2] : 1;
+    const Q first = xr[i0];
+    const int cx = cell_coord(first.x, S.lo[0], S.inv_cs[0], nx);
+    const int cy = cell_coord(first.y, S.lo[1], S.inv_cs[1], ny);
+    const int cz = DIM == 3 ? cell_coord(XR<DIM>::z(first), S.lo[2], S.inv_cs[2], nz) : 0;
+    const int px = S.periodic[0], py = S.periodic[1], pz = DIM == 3 ? S.periodic[2] : 0;
+    const AxisRange ry(cy, ny, py, md), rz(cz, nz, pz, DIM == 3 ? md : 0);
+    // x cells cx-m .. cx+m as one run of keys and, across a periodic boundary, a second one
+    int a0 = cx > md ? cx - md : 0, b0 = cx < nx - 1 - md ? cx + md : nx - 1, a1 = 0, b1 = -1, ix = 0;
+    if (px && cx - md < 0) { a1 = nx + cx - md; b1 = nx - 1; ix = 1; }
+    else if (px && cx + md > nx - 1) { a1 = 0; b1 = cx + md - nx; ix = 2; }
+    const bool img = ix != 0 || (py && (cy - md < 0 || cy + md > ny - 1)) ||
+                     (DIM == 3 && pz && (cz - md < 0 || cz + md > nz - 1));
+    const int nrows = rz.count * ry.count, ntp = (fluid && S.nw > 0) ? 2 : 1;
+    const float inv_ry = __builtin_amdgcn_rcpf((float)ry.count);
+    const double cr2 = S.cand_r2, kh2 = S.kh2;
+    int *__restrict__ out[2] = {A.cand, A.nbr};
+    uint32_t *__restrict__ out_n[2] = {A.ccnt, A.cnt};
+    const int cap[2] = {A.capc, A.cap};
+
+    for (int ib = i0; ib < i1; ib += kCellBatch) {
+        const int np = min(kCellBatch, i1 - ib);
+        // uniform, in vector registers (they would not fit the scalar ones)
+        double xp[kCellBatch], yp[kCellBatch], zp[kCellBatch];
+        int zero = 0;
+        asm("" : "+v"(zero));
+#pragma unroll
+        for (int p = 0; p < kCellBatch; ++p) {
+            const Q q = xr[ib + min(p, np - 1) + zero];
+            xp[p] = q.x;
+            yp[p] = q.y;
+            zp[p] = XR<DIM>::z(q);
+        }
+        if (lane < np) {
+            const Q q = xr[ib + lane];
+            const double pos3[3] = {q.x, q.y, XR<DIM>::z(q)};
+            write_pos_record<T, DIM>(S, A.prec, ib + lane, pos3);
+        }
+        int pend[2][kCellBatch];  // entries waiting in LDS
+#pragma unroll
+        for (int p = 0; p < kCellBatch; ++p) pend[0][p] = pend[1][p] = 0;
+        int done[2] = {0, 0}, nfl[2] = {0, 0};  // of this lane's particle pl: entries stored; fluid entries
+        // 2^sh >= np particles side by side in a store
+        const int sh = np <= 2 ? 1 : (np <= 4 ? 2 : 3), pl = lane & ((1 << sh) - 1);
+        auto per_lane = [&](const int (&v)[kCellBatch]) __attribute__((always_inline)) {  // v[pl]
+            int r = 0;
+#pragma unroll
+            for (int p = 0; p < kCellBatch; ++p) {
+                const int u = __builtin_amdgcn_readfirstlane(v[p]);  // uniform; keeps v in registers
+                r = pl == p ? u : r;
+            }
+            return r;
+        };
+        auto below = [](unsigned long long m) {  // set bits below this lane's
+            return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        };
+        auto most_of = [&](const int (&v)[kCellBatch]) __attribute__((always_inline)) {
+            int m = 0;
+#pragma unroll
+            for (int p = 0; p < kCellBatch; ++p) m = max(m, v[p]);
+            return m;
+        };
+        auto store = [&](auto list) __attribute__((always_inline)) {  // the waiting entries of a list
+            constexpr int l = decltype(list)::value;
+            const int most = most_of(pend[l]), mine = per_lane(pend[l]);
+            for (int r0 = 0; r0 < most; r0 += 64 >> sh) {
+                const int q = r0 + (lane >> sh), r = done[l] + q;
+                if (pl < np && q < mine && r < cap[l])
+                    out[l][(size_t)(unsigned)r * (unsigned)N + (ib + pl)] = lds[wave][l][pl][q];
+            }
+            done[l] += mine;
+#pragma unroll
+            for (int p = 0; p < kCellBatch; ++p) pend[l][p] = 0;
+        };
+        for (int tp = 0; tp < ntp; ++tp) {
+            for (int r0 = 0; r0 < nrows; r0 += 32) {
+                // lane 2q + h: run h of row r0 + q
+                const int r = r0 + (lane >> 1), h = lane & 1;
+                int b = 0, len = 0, im = 0;
+                if (r < nrows && (h == 0 || ix != 0)) {
+                    const int u = DIM == 3 ? (int)(((float)r + 0.5f) * inv_ry) : 0, v = r - u * ry.count;
+                    const int row = S.key_base + (tp ? A.C : 0) + (rz.at(u) * ny + ry.at(v)) * nx;
+                    b = (int)cstart[row + (h ? a1 : a0)];
+                    len = (int)cstart[row + (h ? b1 : b0) + 1] - b;
+                    if (img) {
+                        const int wy = ry.first + v, wz = rz.first + u;
+                        im = (h ? ix : 0) + (py ? 3 * (wy < 0 ? 1 : (wy >= ny ? 2 : 0)) : 0) +
+                             (pz ? 9 * (wz < 0 ? 1 : (wz >= nz ? 2 : 0)) : 0);
+                    }
+                }
+                const int incl = wave_scan(len);
+                const int delta = b - (incl - len);  // slot of candidate t of the run: t + delta
+                const int total = __builtin_amdgcn_readlane(incl, 63);
+                for (int t0 = 0; t0 < total; t0 += 64) {
+                    const int t = t0 + lane;
+                    int run = 0;  // the first run whose end lies beyond t
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) run += __shfl(incl, run + o - 1, 64) <= t ? o : 0;
+                    const bool live = t < total;
+                    const int off = __shfl(delta, run, 64);  // (every lane: its source may lie past the total)
+                    const int j = live ? t + off : i0;
+                    const Q q = xr[j];
+                    double sx = 0.0, sy = 0.0, sz = 0.0;
+                    if (img) {
+                        const int m = __shfl(im, run, 64), mx = m % 3, my = (m / 3) % 3, mz = m / 9;
+                        sx = mx == 1 ? S.L[0] : (mx == 2 ? -S.L[0] : 0.0);
+                        sy = my == 1 ? S.L[1] : (my == 2 ? -S.L[1] : 0.0);
+                        if (DIM == 3) sz = mz == 1 ? S.L[2] : (mz == 2 ? -S.L[2] : 0.0);
+                    }
+                    auto test = [&](auto shifted) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int p = 0; p < kCellBatch; ++p)
+                            if (p < np) {
+#pragma clang fp contract(off)
+                                double dx = xp[p] - q.x, dy = yp[p] - q.y;
+                                double dz = DIM == 3 ? zp[p] - XR<DIM>::z(q) : 0.0;
+                                if constexpr (decltype(shifted)::value) {
+                                    dx = dx + sx;
+                                    dy = dy + sy;
+                                    if (DIM == 3) dz = dz + sz;
+                                }
+                                double r2 = dx * dx + dy * dy;
+                                if (DIM == 3) r2 = r2 + dz * dz;
+                                const bool in_c = live && r2 < cr2 && j != ib + p;
+                                const bool in_x = in_c && r2 < kh2;
+                                const unsigned long long mc = __builtin_amdgcn_ballot_w64(in_c);
+                                const unsigned long long mx = __builtin_amdgcn_ballot_w64(in_x);
+                                if (in_c) lds[wave][0][p][pend[0][p] + below(mc)] = j;
+                                if (in_x) lds[wave][1][p][pend[1][p] + below(mx)] = j;
+                                pend[0][p] += __popcll(mc);
+                                pend[1][p] += __popcll(mx);
+                            }
+                    };
+                    if (img) test(std::true_type());
+                    else test(std::false_type());
+                    if (most_of(pend[0]) > kCellRows - 64) store(Cand());
+                    if (most_of(pend[1]) > kCellRows - 64) store(Exact());
+                }
+            }
+            if (tp == 0) {
+                nfl[0] = done[0] + per_lane(pend[0]);
+                nfl[1] = done[1] + per_lane(pend[1]);
+            }
+        }
+        auto close = [&](auto list) __attribute__((always_inline)) {
+            constexpr int l = decltype(list)::value;
+            store(list);
+            if (lane < np) {  // here pl = lane
+                const int total = done[l];
+                int nf = nfl[l], rest = total - nf;
+                if (total > cap[l]) {
+                    atomicOr(&A.flags[F_NBR_OVERFLOW], 1);
+                    atomicMax(&A.flags[F_NBR_NEEDED], total);
+                    nf = nf < cap[l] ? nf : cap[l];
+                    rest = cap[l] - nf < rest ? cap[l] - nf : rest;
+                }
+                out_n[l][ib + lane] = (uint32_t)nf | ((uint32_t)rest << 16);
+            }
+        };
+        close(Cand());
+        close(Exact());
     }
 }
 
@@ -916,7 +1136,7 @@ __global__ void __launch_bounds__(kTileThreads) k_nbr_tile(NbrArgs<T> A, const i
         const Probe<2> P = make_probe<2>(S, me.x, me.y, 0.0);
         {
             const double pos3[3] = {P.xi, P.yi, 0.0};
-            write_pos_record<T>(S, A.prec, i, pos3);
+            write_pos_record<T, 2>(S, A.prec, i, pos3);
         }
         const int cx = cell_coord(P.xi, S.lo[0], S.inv_cs[0], nx);
         const int cy = cell_coord(P.yi, S.lo[1], S.inv_cs[1], ny);
@@ -1022,37 +1242,70 @@ __global__ void __launch_bounds__(kTileThreads) k_nbr_tile(NbrArgs<T> A, const i
 
 inline int grid_for(int n) { return n > 0 ? ceil_div(n, kThreads) : 1; }
 
-template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a, bool filter)
+template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a, bool filter, bool general_only)
 {
     const dim3 grid(grid_for((int)std::min<int64_t>((int64_t)a.N * G, INT32_MAX)));
-    if (filter) DTSPH_LAUNCH(c, (k_filter<T, DIM, G>), grid, dim3(kThreads), 0, c.stream, a);
-    else DTSPH_LAUNCH(c, (k_nbr<T, DIM, G>), grid, dim3(kThreads), 0, c.stream, a);
+    if (filter) DTSPH_LAUNCH(c, (k_filter<T, DIM, G>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
+    else {
+        if (c.grid_fast && !general_only) DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, false>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
+        if (c.grid_general) DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, true>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
+    }
+}
+
+// Neighbour kernel of a context that was not tuned: one wavefront per cell (64) in 3D
+// (full builds of 262k particles, FP32: 414 us against 453 with 2 lanes per particle, the
+// best lane count; 104k, FP64: 204 against 292) and in 2D up to 20k particles (2.5k: 33
+// against 40 us with 8 lanes; 11.6k: 42 against 48; 25k: 50 both; 160k: 134 against 88 with 2
+// lanes), unless most cells are empty (the 0.5M-particle dam break has 1.5M: 881 against 228
+// us); otherwise the lanes per particle that measured best (25k: 8 lanes 50 us, 4 lanes 52; 160k: 2
+// lanes 88, 4 lanes 98; 300k: 2 lanes 181, 1 lane 190; 2.6M: 1 lane).
+int nbr_lanes_for(const Ctx &c)
+{
+    if ((c.max_dim == 3 || c.N < 20000) && c.C <= c.N) return 64;
+    return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 ? 2 : 1;
 }
 
 // lanes per particle in the neighbour kernels: the autotuner's choice, else
-// enough threads for ~8 waves per SIMD
+// nbr_lanes_for; the filter enough threads for ~8 waves per SIMD
 template <typename T> void launch_grouped(Ctx &c, const NbrArgs<T> &a, bool filter)
 {
+    bool general_only = false;
     if (!filter && c.nbr_tiles && c.n_strips > 0) {
         const size_t lds = (size_t)c.tile_pmax * (sizeof(double2) + sizeof(int)) + (size_t)c.tile_offmax * sizeof(int);
         DTSPH_LAUNCH(c, k_nbr_tile<T>, dim3(c.n_strips), dim3(kTileThreads), lds, c.stream, a, c.strips, c.tile_pmax);
         return;
     }
     int g = filter ? c.g_filter : c.g_nbr;
+    if (!filter && g <= 0) g = nbr_lanes_for(c);
+    if (g == 64) {
+        const int blocks = 8 * ceil_div(ceil_div(c.C, kThreads / 64), 8);  // of one cell type
+        const dim3 grid(c.any_walls ? 2 * blocks : blocks);
+        if (c.grid_fast) {
+            if (c.max_dim == 2)
+                DTSPH_LAUNCH(c, (k_nbr_cell<T, 2>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
+                             (const double2 *)c.xr, c.n_sims, blocks);
+            else
+                DTSPH_LAUNCH(c, (k_nbr_cell<T, 3>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
+                             (const double4 *)c.xr, c.n_sims, blocks);
+        }
+        if (!c.grid_general) return;
+        general_only = true;
+        g = 8;
+    }
     if (g <= 0) {
         g = 1;
         while (g < 8 && (int64_t)g * a.N < (int64_t)256 * 2048) g *= 2;
     }
     if (c.max_dim == 2) {
-        if (g == 1) launch_g<T, 2, 1>(c, a, filter);
-        else if (g == 2) launch_g<T, 2, 2>(c, a, filter);
-        else if (g == 4) launch_g<T, 2, 4>(c, a, filter);
-        else launch_g<T, 2, 8>(c, a, filter);
+        if (g == 1) launch_g<T, 2, 1>(c, a, filter, general_only);
+        else if (g == 2) launch_g<T, 2, 2>(c, a, filter, general_only);
+        else if (g == 4) launch_g<T, 2, 4>(c, a, filter, general_only);
+        else launch_g<T, 2, 8>(c, a, filter, general_only);
     } else {
-        if (g == 1) launch_g<T, 3, 1>(c, a, filter);
-        else if (g == 2) launch_g<T, 3, 2>(c, a, filter);
-        else if (g == 4) launch_g<T, 3, 4>(c, a, filter);
-        else launch_g<T, 3, 8>(c, a, filter);
+        if (g == 1) launch_g<T, 3, 1>(c, a, filter, general_only);
+        else if (g == 2) launch_g<T, 3, 2>(c, a, filter, general_only);
+        else if (g == 4) launch_g<T, 3, 4>(c, a, filter, general_only);
+        else launch_g<T, 3, 8>(c, a, filter, general_only);
     }
 }
 

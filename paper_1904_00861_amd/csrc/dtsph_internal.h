@@ -57,6 +57,7 @@ struct SimDev {
     int cell_div;        // cells of side >= (kappa h + skin) / cell_div; blocks of +-cell_div cells
     int tile_w, tile_h;  // cells per strip of the staged neighbour kernel (2D)
     int periodic[3];
+    int general;         // a periodic axis has fewer than 2 cell_div + 3 cells: minimum image per candidate
     int edac_reg_literal;
     double lo[3], hi[3], L[3], halfL[3], cs[3], inv_cs[3];
     double kh2;          // (kappa h)^2, exact neighbour predicate
@@ -110,10 +111,12 @@ struct Ctx {
     int C = 0;               // fluid cells of all sims; keys 0..2C-1
     int C_max = 0;           // C at the finest subdivision (sizes the key tables)
     int cell_div = 2;
+    bool grid_fast = true, grid_general = false;  // sims without / with SimDev::general
     int cap = 0;             // neighbour-list capacity per particle
     int block = 256;
     int lpp = 1;             // lanes per particle in the pair pass
-    int g_nbr = 0, g_filter = 0;  // lanes per particle in the neighbour kernels (0: heuristic)
+    int g_nbr = 0, g_filter = 0;  // lanes per particle in the neighbour kernels (0: heuristic; g_nbr 64: a
+                                  // wavefront per cell)
     // staged-tile neighbour kernel (2D contexts): 1 use it where it applies;
     // strip table {sim, cell type, first row, first column} for the current
     // subdivision, its capacity (the most strips of any subdivision), and the
@@ -357,34 +360,44 @@ struct ApiError {
 
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Runs f(constants) for the sim of every lane, one sim of the wavefront at a time
+// (nearly always one): the constants are then uniform and live in scalar registers,
+// read by scalar loads, instead of a vector load and vector registers per field.
+template <typename F> __device__ __forceinline__ void for_each_sim(int s, const SimDev *__restrict__ sims, F &&f)
+{
+    for (unsigned long long todo = __ballot(1); todo;) {  // uniform
+        int s0 = __builtin_amdgcn_readlane(s, __builtin_ctzll(todo));
+        const bool mine = s == s0;
+        todo &= ~__ballot(mine);
+        asm("" : "+s"(s0));  // hides s == s0: the compiler would index by the lane's own s
+        if (mine) f(sims[s0]);
+    }
+}
+
 // Position record of slot i read by the pair passes: FP32 path 32-bit fixed
 // point per axis, x_q = floor((x - lo) * q_inv) mod 2^32 (exact wrap on periodic
 // axes, whose q_len divides the period); FP64 path the float64 coordinates. Two
 // components in 2D (uint2 / double2), four in 3D (uint4 / double4).
-template <typename T>
-__device__ inline void write_pos_record(const SimDev &S, void *prec, int i, const double xi[3]);
-
-template <>
-__device__ inline void write_pos_record<float>(const SimDev &S, void *prec, int i, const double xi[3])
+template <typename T, int DIM>
+__device__ inline void write_pos_record(const SimDev &S, void *prec, int i, const double xi[3])
 {
-    uint32_t q[4] = {0u, 0u, 0u, 0u};
-    for (int a = 0; a < S.dim; ++a) {
-        // ablation (DTSPH_OPT_ABS32_POSITIONS): the coordinate rounded to float32 first;
-        // the fixed-point difference of two such values is the float32 difference
-        // (exact for neighbours, Sterbenz) rounded once, as in a float32 pipeline
-        const double xa = S.abs32 ? (double)(float)xi[a] : xi[a];
-        double v = floor((xa - S.lo[a]) * S.q_inv[a]);
-        q[a] = (uint32_t)(unsigned long long)(long long)v;
+    if constexpr (sizeof(T) == 4) {
+        uint32_t q[3] = {0u, 0u, 0u};
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            // ablation (DTSPH_OPT_ABS32_POSITIONS): the coordinate rounded to float32 first;
+            // the fixed-point difference of two such values is the float32 difference
+            // (exact for neighbours, Sterbenz) rounded once, as in a float32 pipeline
+            const double xa = S.abs32 ? (double)(float)xi[a] : xi[a];
+            double v = floor((xa - S.lo[a]) * S.q_inv[a]);
+            q[a] = (uint32_t)(unsigned long long)(long long)v;
+        }
+        if constexpr (DIM == 2) ((uint2 *)prec)[i] = make_uint2(q[0], q[1]);
+        else ((uint4 *)prec)[i] = make_uint4(q[0], q[1], q[2], 0u);
+    } else {
+        if constexpr (DIM == 2) ((double2 *)prec)[i] = make_double2(xi[0], xi[1]);
+        else ((double4 *)prec)[i] = make_double4(xi[0], xi[1], xi[2], 0.0);
     }
-    if (S.dim == 2) ((uint2 *)prec)[i] = make_uint2(q[0], q[1]);
-    else ((uint4 *)prec)[i] = make_uint4(q[0], q[1], q[2], 0u);
-}
-
-template <>
-__device__ inline void write_pos_record<double>(const SimDev &S, void *prec, int i, const double xi[3])
-{
-    if (S.dim == 2) ((double2 *)prec)[i] = make_double2(xi[0], xi[1]);
-    else ((double4 *)prec)[i] = make_double4(xi[0], xi[1], xi[2], 0.0);
 }
 
 }  // namespace dtsph

@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(256) k_correct(int N, int Nf, const int *__res
     }
     if (DIM == 2) ((double2 *)xr)[i] = make_double2(xo[0], xo[1]);
     else ((double4 *)xr)[i] = make_double4(xo[0], xo[1], xo[2], 0.0);
-    write_pos_record<T>(S, prec, i, xo);
+    write_pos_record<T, DIM>(S, prec, i, xo);
     vrec[i] = make_rec<T, DIM>(vr, (T)p);
 }
 
@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(256) k_shift_apply(ShiftArgs<T> A)
     A.pm[i] = p;
     if (DIM == 2) ((double2 *)A.xr)[i] = make_double2(xo[0], xo[1]);
     else ((double4 *)A.xr)[i] = make_double4(xo[0], xo[1], xo[2], 0.0);
-    write_pos_record<T>(S, A.prec, i, xo);
+    write_pos_record<T, DIM>(S, A.prec, i, xo);
     A.vrec[i] = make_rec<T, DIM>(v, (T)p);
 }
 

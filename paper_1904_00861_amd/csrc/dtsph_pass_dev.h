@@ -670,7 +670,7 @@ __device__ __forceinline__ void pass_tile_at(const PassArgs<T> &A, const SimDev 
                     if (S.periodic[d]) e = e > S.halfL[d] ? e - S.L[d] : (e < -S.halfL[d] ? e + S.L[d] : e);
                     e2 += e * e;
                 }
-                write_pos_record<T>(S, ppar ? const_cast<void *>(A.prec) : A.prec2, i, xo);
+                write_pos_record<T, DIM>(S, ppar ? const_cast<void *>(A.prec) : A.prec2, i, xo);
                 if (DIM == 2) ((double2 *)A.xr)[i] = make_double2(xo[0], xo[1]);
                 else ((double4 *)A.xr)[i] = make_double4(xo[0], xo[1], xo[2], 0.0);
                 const double lim = 0.45 * S.skin;
