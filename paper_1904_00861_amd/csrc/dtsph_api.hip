@@ -547,15 +547,16 @@ void check_host_flags(Ctx &c)
                                         "box or clumped); particle state is undefined");
 }
 
-// Wait until the last finalize has published every sim's report: spin on the
-// per-sim sequence words in mapped memory (each written after its report, behind
-// a system-scope fence), asking the stream for errors now and then.
-void wait_reports(Ctx &c)
+// Wait until the finalize launch with sequence number `want` (c.seq: the last one)
+// has published every sim's report: spin on the per-sim sequence words in mapped
+// memory (each written after its report, behind a system-scope fence), asking the
+// stream for errors now and then.
+void wait_reports(Ctx &c, int want)
 {
     const volatile int *seq = c.seq_host;
     auto seen = [&]() {
         for (int s = 0; s < c.n_sims; ++s)
-            if (seq[s] != c.seq) return false;
+            if ((int)((unsigned)seq[s] - (unsigned)want) < 0) return false;
         return true;
     };
     if (c.static_mode) {  // no mapped memory: wait for the stream, then copy
@@ -693,6 +694,8 @@ void shift_decision(Ctx &c, bool use_cand)
     c.records_fresh = true;  // k_shift_apply rewrote the records
 }
 
+constexpr int kWindowLarge = 131072;  // particles from which launch_window goes by single iterations
+
 // A pseudo-time loop: set-up, chunks of iterations with a stop check after each,
 // and the bookkeeping at its end.
 struct LoopRun {
@@ -701,6 +704,12 @@ struct LoopRun {
     bool queued = false;  // the speculative launches follow the latest chunk
     bool split = false;   // the first chunk ends early for a tail launch
     int tries = 0;
+    // single sims: groups of iterations kept two ahead of the reports (launch_window)
+    bool window = false;
+    int group = 1, predict = 1;
+    int known = 0;        // iterations after which a report has been read
+    int flying = 0;       // published groups not read yet: their sequence numbers and iterations
+    int mark_seq[2] = {0, 0}, mark_it[2] = {0, 0};
 };
 
 // Length of a loop's first chunk: the last loop's longest (at most 64). A
@@ -761,6 +770,9 @@ template <typename T> void loop_prologue(Ctx &c, int fixed, LoopRun &L)
         for (auto &d : c.desc) L.max_it = std::max(L.max_it, (int)d.max_iter);
     L.launched = 0;
     L.chunk = first_chunk(c, L.max_it, &L.split);
+    L.window = c.n_sims == 1 && c.chunk == 0 && !c.graphs && !c.speculate;
+    L.group = fixed > 0 ? std::min(fixed, 64) : (c.Nf < kWindowLarge ? 2 : 1);
+    L.predict = fixed > 0 ? fixed : std::max(1, c.last_iters);
     const int expect = fixed > 0 ? fixed : c.last_iters;
     bool fits = false;
     if (c.pair_cache == 2) {
@@ -778,10 +790,9 @@ template <typename T> void loop_prologue(Ctx &c, int fixed, LoopRun &L)
 // updates filter the lists before each wall pass).
 bool fused_walls(const Ctx &c) { return c.Nw > 0 && !c.any_move2; }
 
-// The next chunk of iterations (its size: L.chunk, capped by the iteration limit).
-template <typename T> void launch_chunk(Ctx &c, LoopRun &L)
+// The next n iterations; the last one publishes the reports.
+template <typename T> void launch_iterations(Ctx &c, LoopRun &L, int n)
 {
-    const int n = std::min(L.chunk, L.max_it - L.launched);
     const bool fuse = fused_walls(c);
     for (int k = 0; k < n; ++k) {
         c.pass_index = L.launched + k;
@@ -795,11 +806,38 @@ template <typename T> void launch_chunk(Ctx &c, LoopRun &L)
         launch_pass<T>(c, MODE_PSEUDO);
         if (c.cache_phase == 1) c.coef_valid = true;
         c.cache_phase = 0;
-        // the chunk's last one publishes the reports
         if (fuse) launch_finalize_wall<T>(c, k == n - 1, L.launched + k + 1);
         else launch_finalize(c, k == n - 1);
     }
     L.launched += n;
+}
+
+// The loop of a single sim: groups of iterations, two of them in flight, so that the
+// GPU works on one while the host reads the report of the other; up to the last
+// loop's count no further (a loop that needs as many stops there), past it always two.
+// A group takes longer than the host needs for a report and the next launches
+// (about 15 us), so single iterations from kWindowLarge particles on. Chunks of the last
+// loop's length with a wait after each left the launches after the stop to run empty
+// (two kernels of 2-4 us each, a third of all iterations launched on the 518k dam break
+// and the 2.5k vortex) and the GPU idle for 10-25 us at each chunk's end.
+template <typename T> void launch_window(Ctx &c, LoopRun &L)
+{
+    while (L.flying < 2) {
+        int limit = std::min(L.known + 2 * L.group, L.max_it);
+        if (L.known < L.predict) limit = std::min(limit, L.predict);
+        const int n = std::min(L.group, limit - L.launched);
+        if (n <= 0) return;
+        launch_iterations<T>(c, L, n);
+        L.mark_seq[L.flying] = c.seq;
+        L.mark_it[L.flying++] = L.launched;
+    }
+}
+
+// The next chunk of iterations (its size: L.chunk, capped by the iteration limit).
+template <typename T> void launch_chunk(Ctx &c, LoopRun &L)
+{
+    if (L.window) launch_window<T>(c, L);
+    else launch_iterations<T>(c, L, std::min(L.chunk, L.max_it - L.launched));
 }
 
 // Waits for the chunk in flight, launches more until every sim has stopped, and
@@ -807,8 +845,14 @@ template <typename T> void launch_chunk(Ctx &c, LoopRun &L)
 template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep)
 {
     for (;;) {
-        wait_reports(c);  // k_finalize wrote the mapped reports
+        wait_reports(c, L.window ? L.mark_seq[0] : c.seq);  // k_finalize wrote the mapped reports
         check_host_flags(c);
+        if (L.window) {
+            L.known = L.mark_it[0];
+            L.mark_seq[0] = L.mark_seq[1];
+            L.mark_it[0] = L.mark_it[1];
+            --L.flying;
+        }
         if (c.shift_pending) {  // the last shift has finished: book its size
             c.shift_pending = false;
             const double mx = *(volatile double *)c.sh_max_h;
@@ -817,7 +861,11 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
         }
         bool all = true;
         for (int s = 0; s < c.n_sims; ++s) all = all && c.flags_host[F_COUNT + s];
-        if (all || L.launched >= L.max_it) break;
+        if (all || (L.window ? L.known : L.launched) >= L.max_it) break;
+        if (L.window) {
+            launch_window<T>(c, L);
+            continue;
+        }
         // more iterations than the last loop needed: chunks grow with the loop
         // (sims that stop inside a chunk leave only no-op launches behind)
         set_active_ranges(c, false);
