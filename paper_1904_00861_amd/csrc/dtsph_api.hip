@@ -531,8 +531,10 @@ void check_host_flags(Ctx &c)
     const int over = c.flags_host[F_NBR_OVERFLOW], need = c.flags_host[F_NBR_NEEDED];
     const int cell = c.flags_host[F_CELL_OVERFLOW], outside = c.flags_host[F_OUTSIDE];
     const int skin = c.flags_host[F_SKIN];
-    for (int k = 0; k < F_COUNT; ++k) c.flags_host[k] = 0;
-    mirror_push_flags(c);
+    if (over || need || cell || outside || skin) {  // (a word the device may be writing is left alone)
+        for (int k = 0; k < F_COUNT; ++k) c.flags_host[k] = 0;
+        mirror_push_flags(c);
+    }
     if (skin)
         throw ApiError(DTSPH_EOVERFLOW, "a particle moving in pseudo-time (move = 2) left the candidate-list skin "
                                         "of its loop; lower dtau or dt");
@@ -547,17 +549,42 @@ void check_host_flags(Ctx &c)
                                         "box or clumped); particle state is undefined");
 }
 
+// Takes sim s's report from mapped memory if it is complete, is that of the finalize
+// launch with sequence number `want` or a later one, and the build flags it names
+// have arrived.
+bool take_report(Ctx &c, int s, int want)
+{
+    const volatile uint32_t *src = (const volatile uint32_t *)(c.mirror_reps + s);
+    if ((int)(src[14] - (uint32_t)want) < 0) return false;
+    MirrorRep r;
+    uint32_t w[16];
+    for (int k = 0; k < 16; ++k) w[k] = src[k];
+    if (w[15] != report_check(w) || (int)(w[14] - (uint32_t)want) < 0) return false;
+    std::memcpy(&r, w, sizeof r);
+    for (int k = 0; k < F_COUNT; ++k)
+        if (((r.state >> (16 + k)) & 1u) && !((const volatile int *)c.flags_host)[k]) return false;
+    HostRep &h = c.reps_host[s];
+    h.iters = r.iters;
+    h.reason = (int)(r.state & 255u);
+    h.done = (int)((r.state >> 8) & 1u);
+    h.rp_mean = r.rp_mean;
+    h.rv_mean = r.rv_mean;
+    h.rp_max = r.rp_max;
+    h.rv_max = r.rv_max;
+    h.disp = r.disp;
+    h.pairs = r.pairs;
+    return true;
+}
+
 // Wait until the finalize launch with sequence number `want` (c.seq: the last one)
-// has published every sim's report: spin on the per-sim sequence words in mapped
-// memory (each written after its report, behind a system-scope fence), asking the
-// stream for errors now and then.
+// has published every sim's report: spin on the reports in mapped memory, asking
+// the stream for errors now and then.
 void wait_reports(Ctx &c, int want)
 {
-    const volatile int *seq = c.seq_host;
+    int next = 0;  // sims below it: report taken
     auto seen = [&]() {
-        for (int s = 0; s < c.n_sims; ++s)
-            if ((int)((unsigned)seq[s] - (unsigned)want) < 0) return false;
-        return true;
+        while (next < c.n_sims && take_report(c, next, want)) ++next;
+        return next == c.n_sims;
     };
     if (c.static_mode) {  // no mapped memory: wait for the stream, then copy
         DTSPH_HIP_CHECK(hipStreamSynchronize(c.stream));
@@ -565,13 +592,14 @@ void wait_reports(Ctx &c, int want)
         if (!seen()) throw ApiError(DTSPH_EHIP, "finalize completed without publishing its reports");
         return;
     }
-    for (long spins = 1;; ++spins) {
+    for (long spins = 1, after = 0;; ++spins) {
         if (seen()) break;
         __builtin_ia32_pause();
         if ((spins & 1023) == 0) {
             const hipError_t e = hipStreamQuery(c.stream);
             if (e == hipSuccess) {
                 if (seen()) break;
+                if (++after < 1000) continue;  // the last writes may still be on their way
                 throw ApiError(DTSPH_EHIP, "the loop's launches completed without publishing every report "
                                            "(a tail launch's barrier wait gave up, or a kernel failed)");
             }
@@ -625,8 +653,8 @@ template <typename T> void do_predict(Ctx &c)
     c.p_half = false;
 }
 
-// Tile ranges of the sims whose loop is still running (from the stop flags in
-// mapped memory); every tile when all run or the ranges do not fit.
+// Tile ranges of the sims whose loop is still running (from the last
+// reports); every tile when all run or the ranges do not fit.
 void set_active_ranges(Ctx &c, bool all)
 {
     c.n_ranges = 0;
@@ -635,7 +663,7 @@ void set_active_ranges(Ctx &c, bool all)
     int n = 0, at = 0;
     int2 r[kMaxRanges];
     for (int s = 0; s < c.n_sims; ++s) {
-        if (c.flags_host[F_COUNT + s]) continue;
+        if (c.reps_host[s].done) continue;
         const int tb = c.sims_h[s].tile_begin, te = c.sims_h[s].tile_end;
         if (te <= tb) continue;
         if (n > 0 && r[n - 1].x + (at - r[n - 1].y) == tb) {
@@ -777,7 +805,7 @@ template <typename T> void loop_prologue(Ctx &c, int fixed, LoopRun &L)
     bool fits = false;
     if (c.pair_cache == 2) {
         double entries = 0.0;  // list entries of the fluid, from the last reports
-        for (int s = 0; s < c.n_sims; ++s) entries += (double)c.pairs_host[s];
+        for (int s = 0; s < c.n_sims; ++s) entries += (double)c.reps_host[s].pairs;
         const double per = (c.precision == DTSPH_FP32 ? 16.0 : 32.0) * (c.any_av ? 1.5 : 1.0);
         fits = entries > 0 && entries * per <= kCacheMaxBytes;
     }
@@ -860,7 +888,7 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
             shift_outcome(c, shift_cand_ok(c, mx, c.shift_pending_cand, c.shift_disp));
         }
         bool all = true;
-        for (int s = 0; s < c.n_sims; ++s) all = all && c.flags_host[F_COUNT + s];
+        for (int s = 0; s < c.n_sims; ++s) all = all && c.reps_host[s].done;
         if (all || (L.window ? L.known : L.launched) >= L.max_it) break;
         if (L.window) {
             launch_window<T>(c, L);
@@ -887,13 +915,13 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
     int status = DTSPH_OK, most = 1;
     bool cand = true;
     for (int s = 0; s < c.n_sims; ++s) {
-        const MirrorRep &it = c.reps_host[s];
+        const HostRep &it = c.reps_host[s];
         // r^{n+1} - r^(0) = dt/2 (V^{n+1} - V^(0)): within skin/2 (with margin) the
         // candidate lists built at r^(0) still hold every neighbour at r^{n+1}
         cand = cand && c.sims_h[s].skin > 0 && it.disp < 0.4 * c.sims_h[s].skin;
         c.last_disp[s] = it.disp;
         c.tstats.last_disp = s == 0 ? it.disp : std::max(c.tstats.last_disp, it.disp);
-        const int64_t pairs = (int64_t)c.pairs_host[s];
+        const int64_t pairs = (int64_t)c.reps_host[s].pairs;
         most = std::max(most, it.iters);
         if (rep) {
             rep[s].iters = it.iters;
@@ -913,7 +941,7 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
         int64_t pairs = 0, parts = 0;
         for (int s = 0; s < c.n_sims; ++s)
             if (pt.first < c.reps_host[s].iters) {
-                pairs += (int64_t)c.pairs_host[s];
+                pairs += (int64_t)c.reps_host[s].pairs;
                 parts += c.nf[s];
             }
         if (pairs == 0) continue;  // a launch after every sim had stopped
@@ -1067,7 +1095,7 @@ bool gate_open(const Ctx &c)
 {
     if (!c.cand_next) return false;
     for (int s = 0; s < c.n_sims; ++s)
-        if (!c.flags_host[F_COUNT + s] || c.reps_host[s].reason == DTSPH_NONFINITE) return false;
+        if (!c.reps_host[s].done || c.reps_host[s].reason == DTSPH_NONFINITE) return false;
     return true;
 }
 
@@ -1362,11 +1390,10 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
         }
         c.last_disp.assign(n_sims, 0.0);
         {
-            const size_t fb_bytes = (sizeof(int) * (F_COUNT + n_sims) + 15) / 16 * 16;
-            const size_t pb_bytes = 8 * (size_t)n_sims;
-            const size_t rb_bytes = (sizeof(MirrorRep) * n_sims + 15) / 16 * 16;
-            const size_t sq_bytes = (sizeof(int) * n_sims + 15) / 16 * 16;
-            const size_t bytes = fb_bytes + pb_bytes + rb_bytes + sq_bytes + 16;
+            // build flags and the largest shift (64 bytes), then the reports
+            static_assert(sizeof(int) * F_COUNT <= 32, "the largest shift sits at byte 32");
+            const size_t bytes = 64 + sizeof(MirrorRep) * (size_t)n_sims;
+            c.reps_host.assign(n_sims, HostRep());
             void *md = nullptr;
             if (c.static_mode) {
                 // device memory in the scratch, copied to a static host buffer after each sync
@@ -1388,15 +1415,11 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
             }
             char *hb = (char *)c.mirror_h, *db = (char *)md;
             c.flags_host = (int *)hb;
-            c.pairs_host = (unsigned long long *)(hb + fb_bytes);
-            c.reps_host = (MirrorRep *)(hb + fb_bytes + pb_bytes);
+            c.mirror_reps = (MirrorRep *)(hb + 64);
             c.m_flags_d = (int *)db;
-            c.m_pairs_d = (unsigned long long *)(db + fb_bytes);
-            c.m_reps_d = (MirrorRep *)(db + fb_bytes + pb_bytes);
-            c.seq_host = (int *)(hb + fb_bytes + pb_bytes + rb_bytes);
-            c.m_seq_d = (int *)(db + fb_bytes + pb_bytes + rb_bytes);
-            c.sh_max_h = (double *)(hb + fb_bytes + pb_bytes + rb_bytes + sq_bytes);
-            c.sh_max_d = (double *)(db + fb_bytes + pb_bytes + rb_bytes + sq_bytes);
+            c.m_reps_d = (MirrorRep *)(db + 64);
+            c.sh_max_h = (double *)(hb + 32);
+            c.sh_max_d = (double *)(db + 32);
         }
         DTSPH_HIP_CHECK(hipMemcpy(c.init_slot, init_slot.data(), sizeof(int) * 2 * N, hipMemcpyHostToDevice));
         DTSPH_HIP_CHECK(hipMemset(c.flags, 0, sizeof(int) * (F_COUNT + n_sims)));

@@ -97,10 +97,34 @@ struct SimIter {
     long long pairs;  // fluid-row neighbour pairs of the last iteration
 };
 
-// Per-sim report as published to mapped host memory.
-struct MirrorRep {
-    int iters, reason;
+// Per-sim report as published to mapped host memory: one 64-byte line that carries
+// its own proof of being complete. Device writes to different lines of host memory
+// can become visible out of order (a fence between them does not prevent it: a
+// separate stop flag was read stale once in about 10^4 loops, which ended the loop
+// there), so the host takes a line only when its check word fits the rest of it.
+struct alignas(64) MirrorRep {
     double rp_mean, rv_mean, rp_max, rv_max, disp;
+    long long pairs;
+    int iters;
+    uint32_t state;   // bits 0..7 stop reason, 8 stopped, 16.. build flags moved with this report
+    uint32_t seq;     // the sim's count of published reports
+    uint32_t check;   // report_check of the 15 words before it
+};
+static_assert(sizeof(MirrorRep) == 64, "one line");
+
+__host__ __device__ inline uint32_t report_check(const uint32_t w[16])
+{
+    uint32_t h = 0x2545f491u;
+#pragma unroll
+    for (int k = 0; k < 15; ++k) h = (h ^ w[k]) * 0x9e3779b1u + (h >> 15);
+    return h;
+}
+
+// A report as the host has taken it.
+struct HostRep {
+    int iters = 0, reason = 0, done = 0;
+    double rp_mean = 0, rv_mean = 0, rp_max = 0, rv_max = 0, disp = 0;
+    long long pairs = 0;
 };
 
 // Context (host object owning device memory).
@@ -248,16 +272,13 @@ struct Ctx {
     int *done_dev = nullptr;
     int *init_slot = nullptr;             // caller index -> slot before any sort
 
-    // mapped host memory written by k_publish (host and device views)
+    // mapped host memory written by the reports and k_publish (host and device views)
     void *mirror_h = nullptr;
-    int *flags_host = nullptr;             // F_COUNT flags then n_sims stop flags
-    MirrorRep *reps_host = nullptr;
-    unsigned long long *pairs_host = nullptr;
+    int *flags_host = nullptr;             // F_COUNT build flags
+    MirrorRep *mirror_reps = nullptr;
     int *m_flags_d = nullptr;
     MirrorRep *m_reps_d = nullptr;
-    unsigned long long *m_pairs_d = nullptr;
-    int *seq_host = nullptr;              // per sim: sequence number of the last finalize
-    int *m_seq_d = nullptr;
+    std::vector<HostRep> reps_host;       // the last reports taken, per sim
     int seq = 0;                          // last finalize launched
 
     // timing

@@ -435,9 +435,7 @@ void launch_gate(Ctx &c)
 
 void launch_publish(Ctx &c)
 {
-    const int n = F_COUNT + c.n_sims;
-    DTSPH_LAUNCH(c, k_publish, dim3(grid_for(n)), dim3(256), 0, c.stream, c.n_sims, c.flags, c.iters,
-                       c.m_flags_d, c.m_reps_d, c.m_pairs_d);
+    DTSPH_LAUNCH(c, k_publish, dim3(1), dim3(64), 0, c.stream, c.flags, c.m_flags_d);
     DTSPH_HIP_CHECK(hipGetLastError());
 }
 

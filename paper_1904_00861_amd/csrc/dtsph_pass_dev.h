@@ -887,8 +887,8 @@ __global__ void __launch_bounds__(256) k_wall(WallArgs<T> A)
 // Two levels in one launch: workgroup g reduces the partials of segment g (up to
 // kSegTiles tiles of one sim, fixed order); the last segment of a sim to arrive
 // (per-sim ticket) reduces that sim's segment sums in segment order, applies the
-// stop test and writes the sim's report and stop flag into mapped host memory
-// (moving any build flag there too), so the host only needs a stream sync.
+// stop test and writes the sim's report into mapped host memory (moving any build
+// flag there too), where the host polls for it.
 // Which workgroup arrives last does not change any sum.
 struct FinArgs {
     const SimDev *sims;
@@ -903,25 +903,26 @@ struct FinArgs {
     int n_sims;
     int *h_flags;
     MirrorRep *h_reps;
-    unsigned long long *h_pairs;
-    int *h_seq;      // per sim: its count of published reports, once this one is visible
     uint32_t *pubcount;
     int publish;     // 0: device state only (not the last iteration of a chunk)
 };
 
 constexpr int kFinThreads = kSegTiles;
 
-// Build flags move to mapped memory with sim 0's report (same thread, before
-// its sequence word).
-__device__ inline void move_build_flags(const FinArgs &A)
+// Build flags move to mapped memory with sim 0's report, which names them: the host
+// waits for those. Returns their bits.
+__device__ inline uint32_t move_build_flags(const FinArgs &A)
 {
+    uint32_t moved = 0;
     for (int k = 0; k < F_COUNT; ++k) {
         const int f = A.flags[k];
         if (f) {
             A.h_flags[k] = f;
             A.flags[k] = 0;
+            moved |= 1u << k;
         }
     }
+    return moved;
 }
 
 // Fixed-order workgroup reduction of {sum, sum, max, max, max, sum}; result in
@@ -954,26 +955,31 @@ __device__ inline void fin_block_reduce(double v[6])
     __syncthreads();
 }
 
-// Sim s's report and stop flag (and, with sim 0, the build flags) into mapped
-// memory, then its sequence word behind a system-scope fence.
+// Sim s's report (and, with sim 0, the build flags) into mapped memory.
 __device__ inline void publish_report(const FinArgs &A, int s, const SimIter &It)
 {
-    A.h_flags[F_COUNT + s] = It.done;
-    MirrorRep r;
-    r.iters = It.iters;
-    r.reason = It.reason;
-    r.rp_mean = It.rp_mean;
-    r.rv_mean = It.rv_mean;
-    r.rp_max = It.rp_max;
-    r.rv_max = It.rv_max;
-    r.disp = It.disp;
-    A.h_reps[s] = r;
-    A.h_pairs[s] = (unsigned long long)It.pairs;
-    if (s == 0) move_build_flags(A);
+    uint32_t w[16];
+    auto put = [&](int k, double v) {
+        w[k] = (uint32_t)__double2loint(v);
+        w[k + 1] = (uint32_t)__double2hiint(v);
+    };
+    put(0, It.rp_mean);
+    put(2, It.rv_mean);
+    put(4, It.rp_max);
+    put(6, It.rv_max);
+    put(8, It.disp);
+    w[10] = (uint32_t)It.pairs;
+    w[11] = (uint32_t)((unsigned long long)It.pairs >> 32);
+    w[12] = (uint32_t)It.iters;
+    const uint32_t moved = s == 0 ? move_build_flags(A) : 0u;
+    w[13] = (uint32_t)It.reason | (It.done ? 256u : 0u) | (moved << 16);
     const uint32_t q = A.pubcount[s] + 1u;  // one publishing thread per sim and launch
     A.pubcount[s] = q;
-    __threadfence_system();
-    A.h_seq[s] = (int)q;
+    w[14] = q;
+    w[15] = report_check(w);
+    uint4 *out = (uint4 *)(A.h_reps + s);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
 }
 
 // What the closing thread needs, read by thread 0 of every workgroup at the
@@ -1163,31 +1169,14 @@ __global__ void __launch_bounds__(256) k_wall_pressure(int Nw, int Nf, const int
     pwall[iw] = dim == 2 ? r.z : r.w;
 }
 
-// Copy the host-visible control words (build flags, stop flags, per-sim reports
-// and pair counts) into mapped host memory, so one stream sync makes them
+// Move the build flags to mapped host memory, so one stream sync makes them
 // readable without a separate copy.
-__global__ void k_publish(int n_sims, int *__restrict__ flags, const SimIter *__restrict__ iters,
-                          int *__restrict__ h_flags, MirrorRep *__restrict__ h_reps,
-                          unsigned long long *__restrict__ h_pairs)
+__global__ void k_publish(int *__restrict__ flags, int *__restrict__ h_flags)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < F_COUNT && flags[i]) {  // build flags are moved to the host once
+    const int i = threadIdx.x;
+    if (i < F_COUNT && flags[i]) {
         h_flags[i] = flags[i];
         flags[i] = 0;
-    }
-    if (i >= F_COUNT && i < F_COUNT + n_sims) h_flags[i] = flags[i];
-    if (i < n_sims) {
-        const SimIter &It = iters[i];
-        MirrorRep r;
-        r.iters = It.iters;
-        r.reason = It.reason;
-        r.rp_mean = It.rp_mean;
-        r.rv_mean = It.rv_mean;
-        r.rp_max = It.rp_max;
-        r.rv_max = It.rv_max;
-        r.disp = It.disp;
-        h_reps[i] = r;
-        h_pairs[i] = (unsigned long long)It.pairs;
     }
 }
 
@@ -1255,8 +1244,7 @@ FinArgs fin_args(Ctx &c, bool publish)
     a.sims = c.sims; a.iters = c.iters; a.partials = c.partials; a.partials2 = c.partials2;
     a.segs = c.segs; a.seg_p = c.seg_p; a.seg_p2 = c.seg_p2; a.tickets = c.tickets;
     a.done_out = c.done_dev; a.flags = c.flags; a.n_sims = c.n_sims;
-    a.h_flags = c.m_flags_d; a.h_reps = c.m_reps_d; a.h_pairs = c.m_pairs_d;
-    a.h_seq = c.m_seq_d;
+    a.h_flags = c.m_flags_d; a.h_reps = c.m_reps_d;
     a.pubcount = c.pubcount;
     a.publish = publish ? 1 : 0;
     if (publish) ++c.seq;  // every sim's count advances once per publishing launch

@@ -348,7 +348,7 @@ bool tail_fits(const Ctx &c)
     if (!tail_kind(c) || c.loop_cached || c.gated || c.replay) return false;
     int64_t tiles = 0;
     for (int s = 0; s < c.n_sims; ++s) {
-        if (c.flags_host[F_COUNT + s]) continue;
+        if (c.reps_host[s].done) continue;
         const int nt = c.sims_h[s].tile_end - c.sims_h[s].tile_begin;
         if (nt <= 0 || nt > kTailSimTiles) return false;
         tiles += nt;
@@ -386,7 +386,7 @@ template <typename T> bool launch_tail(Ctx &c, int k0)
     L.part2[1] = c.tail_part2;
     for (int q = 0; q < kTailMaxSims / 32; ++q) L.outside[q] = 0u;
     for (int s = 0; s < c.n_sims; ++s)
-        if (c.flags_host[F_COUNT + s]) L.outside[s >> 5] |= 1u << (s & 31);
+        if (c.reps_host[s].done) L.outside[s >> 5] |= 1u << (s & 31);
     const int nw = c.n_sims + 1 + c.n_tiles / kTailGroup + c.n_sims + 1;  // arrivals, error, groups
     hipLaunchKernelGGL(k_tail_zero, dim3((nw + 255) / 256), dim3(256), 0, c.stream, c.tail_words, nw);
     DTSPH_HIP_CHECK(hipGetLastError());
