@@ -366,6 +366,7 @@ SimDev make_simdev(const dtsph_sim_desc &d, int64_t nf, int64_t nw)
             S.L[a] = d.hi[a] - d.lo[a];
             S.halfL[a] = 0.5 * S.L[a];
             S.periodic[a] = d.periodic[a] ? 1 : 0;
+            S.inv_L[a] = S.periodic[a] ? 1.0 / S.L[a] : 0.0;
             // fixed-point frame: a length q_len maps onto 2^32 units; on periodic
             // axes q_len divides the period so wrap-around is exact
             if (S.periodic[a]) {
@@ -379,6 +380,7 @@ SimDev make_simdev(const dtsph_sim_desc &d, int64_t nf, int64_t nw)
             S.ncell[a] = 1;
             S.cs[a] = S.inv_cs[a] = 1.0;
             S.L[a] = S.halfL[a] = 1.0;
+            S.inv_L[a] = 0.0;
             S.q_len[a] = 1.0;
             S.q_inv[a] = 0.0;
         }

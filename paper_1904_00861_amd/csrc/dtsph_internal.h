@@ -60,6 +60,7 @@ struct SimDev {
     int general;         // a periodic axis has fewer than 2 cell_div + 3 cells: minimum image per candidate
     int edac_reg_literal;
     double lo[3], hi[3], L[3], halfL[3], cs[3], inv_cs[3];
+    double inv_L[3];     // 1 / L on periodic axes, 0 on the others
     double kh2;          // (kappa h)^2, exact neighbour predicate
     double skin, cand_r2; // candidate lists reach kappa h + skin (squared radius)
     double h, inv_h, rho0, mass, c, nu, nu_e;

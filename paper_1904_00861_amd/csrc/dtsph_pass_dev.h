@@ -48,10 +48,34 @@ template <> struct V4<double> { using type = double4; };
 
 template <typename T> __device__ inline T rsq(T x);
 template <> __device__ inline float rsq<float>(float x) { return __builtin_amdgcn_rsqf(x); }
-template <> __device__ inline double rsq<double>(double x) { return 1.0 / sqrt(x); }
+// FP64: the hardware estimate (relative error below 2^-24) and one third-order
+// step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2. Against 64-bit mantissas over 10^-20
+// .. 10^3: at most 0.98 ulp, rms 0.33, where 1.0 / sqrt(x) gives 1.48 and 0.44,
+// in 6 instructions instead of about 35. x > 0. (With rcp and the minimum image
+// below: 104k particles in 3D, 113 neighbours, build and 8 iterations 1129 -> 1042 us.)
+template <> __device__ inline double rsq<double>(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
 template <typename T> __device__ inline T rcp(T x);
 template <> __device__ inline float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
-template <> __device__ inline double rcp<double>(double x) { return 1.0 / x; }
+// FP64: estimate and one third-order step y (1 + e + e^2), e = 1 - x y: at most
+// 0.500 ulp and rms 0.289, as 1.0 / x, over the same range (4 instructions).
+template <> __device__ inline double rcp<double>(double x)
+{
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// a b + c. In FP64 always one rounding, so that every kernel that holds this
+// arithmetic (plain, masked, persistent) computes the same bits; where the
+// compiler chose which product of a sum to fuse, two of them differed in the last
+// place. FP32 keeps the plain expression.
+__device__ inline float mad(float a, float b, float c) { return a * b + c; }
+__device__ inline double mad(double a, double b, double c) { return fma(a, b, c); }
 
 // component access of the {V, p} record: 2D {vx, vy, p, -}, 3D {vx, vy, vz, p}
 template <typename Q> __device__ inline auto comp(const Q &v, int k) { return k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w; }
@@ -90,20 +114,14 @@ template <int DIM> struct Pos<float, DIM> {
 
 template <int DIM> struct Pos<double, DIM> {
     using Rec = typename std::conditional<DIM == 2, double2, double4>::type;
-    double L[3], halfL[3];
-    int per[3];
+    double L[3], inv_L[3];
     __device__ explicit Pos(const SimDev &S)
     {
-        for (int a = 0; a < 3; ++a) { L[a] = S.L[a]; halfL[a] = S.halfL[a]; per[a] = S.periodic[a]; }
+        for (int a = 0; a < 3; ++a) { L[a] = S.L[a]; inv_L[a] = S.inv_L[a]; }
     }
-    __device__ inline double mi(double s, int a) const
-    {
-        if (per[a]) {
-            if (s > halfL[a]) s -= L[a];
-            else if (s < -halfL[a]) s += L[a];
-        }
-        return s;
-    }
+    // minimum image without branches: s - L rint(s / L) (inv_L = 0 on an axis
+    // that is not periodic); the product is exact, so one rounding as in s -+ L
+    __device__ inline double mi(double s, int a) const { return fma(-L[a], rint(s * inv_L[a]), s); }
     __device__ inline void delta(const Rec &a, const Rec &b, double r[3]) const
     {
         r[0] = mi(a.x - b.x, 0);
@@ -171,13 +189,12 @@ __device__ __forceinline__ void pair_terms(const PassConst<T> &K, const T r[3], 
                                            typename V4<T>::type *out = nullptr,
                                            typename AvC<T, DIM>::type *out_av = nullptr)
 {
-    T r2 = r[0] * r[0] + r[1] * r[1];
-    if (DIM == 3) r2 += r[2] * r[2];
+    T r2 = mad(r[0], r[0], r[1] * r[1]);
+    if (DIM == 3) r2 = mad(r[2], r[2], r2);
     const T r2s = r2 > K.tiny ? r2 : K.tiny;
     const T rinv = rsq<T>(r2s);
     const T rr = r2s * rinv;
-    const T q = rr * K.inv_h;
-    T t3 = T(3) - q, t2 = T(2) - q, t1 = T(1) - q;
+    T t3 = mad(-rr, K.inv_h, T(3)), t2 = mad(-rr, K.inv_h, T(2)), t1 = mad(-rr, K.inv_h, T(1));
     t3 = t3 > T(0) ? t3 : T(0);
     t2 = t2 > T(0) ? t2 : T(0);
     t1 = t1 > T(0) ? t1 : T(0);
@@ -185,39 +202,39 @@ __device__ __forceinline__ void pair_terms(const PassConst<T> &K, const T r[3], 
     a *= a;
     b *= b;
     c *= c;
-    const T poly = T(15) * c + (T(-6) * b + a);
+    const T poly = mad(T(15), c, mad(T(-6), b, a));
     const T G = poly * rinv;
     const T rden = rcp<T>(r2 + K.den_v);
     const T pr = poly * rr;
     const T Fv = pr * rden;
     const T Fe = SEPDEN ? pr * rcp<T>(r2 + K.den_e) : Fv;
-    T dotd = vd[0] * r[0] + vd[1] * r[1];
-    if (DIM == 3) dotd += vd[2] * r[2];
-    acc.div += G * dotd;
-    acc.lap += Fe * (pi - pj);
+    T dotd = mad(vd[0], r[0], vd[1] * r[1]);
+    if (DIM == 3) dotd = mad(vd[2], r[2], dotd);
+    acc.div = mad(G, dotd, acc.div);
+    acc.lap = mad(Fe, pi - pj, acc.lap);
     T P = pi + pj;
     T sG = 0;
     if (CONV) {
-        T dvi = av[0] * r[0] + av[1] * r[1];
-        if (DIM == 3) dvi += av[2] * r[2];
+        T dvi = mad(av[0], r[0], av[1] * r[1]);
+        if (DIM == 3) dvi = mad(av[2], r[2], dvi);
         sG = G * dvi;
-        acc.padv += sG * P;
+        acc.padv = mad(sG, P, acc.padv);
     }
     if (AV) {
-        T dotv = vv[0] * r[0] + vv[1] * r[1];
-        if (DIM == 3) dotv += vv[2] * r[2];
+        T dotv = mad(vv[0], r[0], vv[1] * r[1]);
+        if (DIM == 3) dotv = mad(vv[2], r[2], dotv);
         const T phi = dotv * (SEPDEN ? rcp<T>(r2 + K.den_a) : rden);
-        P += K.k_av * (phi < T(0) ? phi : T(0));
+        P = mad(K.k_av, phi < T(0) ? phi : T(0), P);
     }
     const T PG = P * G;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-        acc.vis[d] += Fv * vv[d];
-        acc.grad[d] += PG * r[d];
+        acc.vis[d] = mad(Fv, vv[d], acc.vis[d]);
+        acc.grad[d] = mad(PG, r[d], acc.grad[d]);
     }
     if (CONV) {
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) acc.conv[d] += sG * (T(2) * vi[d] - vv[d]);
+        for (int d = 0; d < DIM; ++d) acc.conv[d] = mad(sG, mad(T(2), vi[d], -vv[d]), acc.conv[d]);
     }
     if (CACHE_OUT) {
         typename V4<T>::type c;
@@ -251,30 +268,30 @@ __device__ __forceinline__ void pair_cached(const PassConst<T> &K, const typenam
                                             const T vi[3], const T av[3], T pi, T pj, Acc<T> &acc)
 {
     const T g[3] = {c.x, c.y, c.z};
-    T dotd = vd[0] * g[0] + vd[1] * g[1];
-    if (DIM == 3) dotd += vd[2] * g[2];
+    T dotd = mad(vd[0], g[0], vd[1] * g[1]);
+    if (DIM == 3) dotd = mad(vd[2], g[2], dotd);
     acc.div += dotd;
-    acc.lap += c.w * (pi - pj);
+    acc.lap = mad(c.w, pi - pj, acc.lap);
     T P = pi + pj;
     T sG = 0;
     if (CONV) {
-        sG = av[0] * g[0] + av[1] * g[1];
-        if (DIM == 3) sG += av[2] * g[2];
-        acc.padv += sG * P;
+        sG = mad(av[0], g[0], av[1] * g[1]);
+        if (DIM == 3) sG = mad(av[2], g[2], sG);
+        acc.padv = mad(sG, P, acc.padv);
     }
     if (AV) {
-        T phi = vv[0] * u.x + vv[1] * u.y;
-        if constexpr (DIM == 3) phi += vv[2] * u.z;
-        P += K.k_av * (phi < T(0) ? phi : T(0));
+        T phi = mad(vv[0], u.x, vv[1] * u.y);
+        if constexpr (DIM == 3) phi = mad(vv[2], u.z, phi);
+        P = mad(K.k_av, phi < T(0) ? phi : T(0), P);
     }
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-        acc.vis[d] += c.w * vv[d];
-        acc.grad[d] += P * g[d];
+        acc.vis[d] = mad(c.w, vv[d], acc.vis[d]);
+        acc.grad[d] = mad(P, g[d], acc.grad[d]);
     }
     if (CONV) {
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) acc.conv[d] += sG * (T(2) * vi[d] - vv[d]);
+        for (int d = 0; d < DIM; ++d) acc.conv[d] = mad(sG, mad(T(2), vi[d], -vv[d]), acc.conv[d]);
     }
 }
 
@@ -626,11 +643,11 @@ __device__ __forceinline__ void pass_tile_at(const PassArgs<T> &A, const SimDev 
 
     T Dv = 0, R[3] = {0, 0, 0}, vt2 = 0, dw2 = 0;
     if (owner) {
-        Dv = (T)S.k_div * acc.div + (T)S.k_lap * acc.lap;
-        for (int d = 0; d < DIM; ++d) R[d] = (T)S.k_grad * acc.grad[d] + (T)S.k_visc * acc.vis[d] + (T)S.g[d];
+        Dv = mad((T)S.k_div, acc.div, (T)S.k_lap * acc.lap);
+        for (int d = 0; d < DIM; ++d) R[d] = mad((T)S.k_grad, acc.grad[d], (T)S.k_visc * acc.vis[d]) + (T)S.g[d];
         if (CONV) {
-            for (int d = 0; d < DIM; ++d) R[d] += (T)S.k_conv * acc.conv[d];
-            Dv += (T)S.k_padv * acc.padv;
+            for (int d = 0; d < DIM; ++d) R[d] = mad((T)S.k_conv, acc.conv[d], R[d]);
+            Dv = mad((T)S.k_padv, acc.padv, Dv);
         }
 
         if (MODE == MODE_PSEUDO) {
@@ -638,18 +655,18 @@ __device__ __forceinline__ void pass_tile_at(const PassArgs<T> &A, const SimDev 
             T vnew[3] = {0, 0, 0}, vtn[3] = {0, 0, 0};
             for (int d = 0; d < DIM; ++d) {
                 const T wk = st_w[d];
-                const T bdf = (T(3) * wk - st_dv[d]) * inv2dt;
+                const T bdf = mad(T(3), wk, -st_dv[d]) * inv2dt;
                 const T dvdtau = (R[d] - bdf) * gamma;
-                const T wn = wk + dtau * dvdtau;
+                const T wn = mad(dtau, dvdtau, wk);
                 const T vt = dt * dvdtau;
                 vtn[d] = vt;
-                vt2 += vt * vt;
+                vt2 = mad(vt, vt, vt2);
                 const T dw = wn - st_w0[d];
-                dw2 += dw * dw;
+                dw2 = mad(dw, dw, dw2);
                 A.w[d * Nf + i] = wn;
                 vnew[d] = st_vn[d] + wn;
             }
-            const double pm = st_pm + S.dtau * (double)Dv;
+            const double pm = mad(S.dtau, (double)Dv, st_pm);
             A.pm[i] = pm;
             A.dp[i] = Dv;
             vout[i] = make_rec<T, DIM>(vnew, (T)pm);
@@ -828,20 +845,20 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
             if (!ok[m]) continue;
             T r[3];
             pos.delta(ri, rj[m], r);
-            T r2 = r[0] * r[0] + r[1] * r[1];
-            if (DIM == 3) r2 += r[2] * r[2];
-            const T q = sqrt(r2) * inv_h;
-            T t3 = T(3) - q, t2 = T(2) - q, t1 = T(1) - q;
+            T r2 = mad(r[0], r[0], r[1] * r[1]);
+            if (DIM == 3) r2 = mad(r[2], r[2], r2);
+            const T rr = sqrt(r2);
+            T t3 = mad(-rr, inv_h, T(3)), t2 = mad(-rr, inv_h, T(2)), t1 = mad(-rr, inv_h, T(1));
             t3 = t3 > T(0) ? t3 : T(0);
             t2 = t2 > T(0) ? t2 : T(0);
             t1 = t1 > T(0) ? t1 : T(0);
             const T a5 = t3 * t3 * t3 * t3 * t3, b5 = t2 * t2 * t2 * t2 * t2, c5 = t1 * t1 * t1 * t1 * t1;
-            const T W = T(15) * c5 + (T(-6) * b5 + a5);  // sigma cancels in the ratios
+            const T W = mad(T(15), c5, mad(T(-6), b5, a5));  // sigma cancels in the ratios
             S0 += W;
-            Sp += pres<DIM>(vj[m]) * W;
+            Sp = mad(pres<DIM>(vj[m]), W, Sp);
             for (int d = 0; d < DIM; ++d) {
-                Srr[d] += rho * r[d] * W;
-                Sv[d] += comp(vj[m], d) * W;
+                Srr[d] = mad(rho * r[d], W, Srr[d]);
+                Sv[d] = mad(comp(vj[m], d), W, Sv[d]);
             }
         }
     }
@@ -850,10 +867,10 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
     T pw = 0;
     if (S0 > T(0)) {
         T gr = 0;
-        for (int d = 0; d < DIM; ++d) gr += (T)S.g[d] * Srr[d];
+        for (int d = 0; d < DIM; ++d) gr = mad((T)S.g[d], Srr[d], gr);
         const T pv = (Sp + gr) / S0;
         pw = pv > T(0) ? pv : T(0);
-        for (int d = 0; d < DIM; ++d) ghost[d] = T(2) * vw[d] - Sv[d] / S0;
+        for (int d = 0; d < DIM; ++d) ghost[d] = mad(T(2), vw[d], -(Sv[d] / S0));
     } else {
         for (int d = 0; d < DIM; ++d) ghost[d] = vw[d];
     }
