@@ -461,7 +461,9 @@ void setup_tiles(Ctx &c)
         for (int t = S.tile_begin, k = 0; t < S.tile_end; t += kSegTiles, ++k)
             segs.push_back(make_int4(s, t, std::min(t + kSegTiles, S.tile_end), k));
         S.seg_count = (int)segs.size() - S.seg_begin;
+        if (S.seg_count == 1) segs.back().w = -1;
     }
+    c.seg0 = segs.empty() ? make_int4(0, 0, 0, 0) : segs[0];
     c.n_tiles = (int)tiles.size();
     c.n_segs = (int)segs.size();
     DTSPH_HIP_CHECK(hipMemcpy(c.tiles, tiles.data(), sizeof(int2) * tiles.size(), hipMemcpyHostToDevice));

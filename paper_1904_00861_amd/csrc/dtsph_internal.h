@@ -254,6 +254,7 @@ struct Ctx {
     int n_tiles = 0;
     int4 *segs = nullptr;                 // per segment: sim, first tile, end tile, index in sim
     int n_segs = 0;
+    int4 seg0{};                          // the first residual segment
     double4 *seg_p = nullptr;             // per segment: partial sums of the residual terms
     double2 *seg_p2 = nullptr;
     uint32_t *tickets = nullptr;          // per sim: segments of the running finalize done

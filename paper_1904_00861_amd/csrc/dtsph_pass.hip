@@ -220,11 +220,11 @@ __global__ void __launch_bounds__(256) k_shift_sums(ShiftArgs<T> A)
                 }
             }
             if (SL > 1) {
-                lane_sum(divr, SL);
+                lane_sum<SL>(divr);
                 for (int a = 0; a < DIM; ++a) {
-                    lane_sum(sd[a], SL);
-                    lane_sum(gp[a], SL);
-                    for (int b = 0; b < DIM; ++b) lane_sum(gv[b][a], SL);
+                    lane_sum<SL>(sd[a]);
+                    lane_sum<SL>(gp[a]);
+                    for (int b = 0; b < DIM; ++b) lane_sum<SL>(gv[b][a]);
                 }
             }
             if (!(divr < T(S.dim) - T(0.5)))  // not on the free surface

@@ -351,9 +351,72 @@ template <typename T> __device__ inline int launch_tile(const PassArgs<T> &A, in
     return first + (v - at);
 }
 
-template <typename T> __device__ inline void lane_sum(T &v, int lpp)
+// Butterfly exchanges within a wavefront without the LDS crossbar: lane ^ O by DPP
+// for O = 1, 2, 4, 8 (quad permutes, half-row mirror of reversed quads, row rotation),
+// lanes ^ 16 and ^ 32 by the row and half swaps, whose two results are the lane's own
+// value and its partner's in either order (combine() must not depend on it). Every
+// lane of the wavefront takes part. A level of six float64 values costs 12
+// dependent-free moves instead of 12 crossbar round trips.
+template <int O> __device__ inline uint32_t xor_lane(uint32_t x)
 {
-    for (int o = lpp >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    static_assert(O == 1 || O == 2 || O == 4 || O == 8, "within a row");
+    if (O == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);
+    if (O == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);
+    if (O == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, true);
+    const int m = __builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true);
+}
+
+template <int O> __device__ inline float xor_lane(float x) { return __uint_as_float(xor_lane<O>(__float_as_uint(x))); }
+
+template <int O> __device__ inline double xor_lane(double x)
+{
+    return __hiloint2double((int)xor_lane<O>((uint32_t)__double2hiint(x)), (int)xor_lane<O>((uint32_t)__double2loint(x)));
+}
+
+template <int O, typename F> __device__ inline double xor_combine(double x, F combine)
+{
+    if constexpr (O <= 8) {
+        return combine(x, xor_lane<O>(x));
+    } else {
+        const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+        double a, b;
+        if constexpr (O == 16) {
+            const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            a = __hiloint2double((int)h[0], (int)l[0]);
+            b = __hiloint2double((int)h[1], (int)l[1]);
+        } else {
+            const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            a = __hiloint2double((int)h[0], (int)l[0]);
+            b = __hiloint2double((int)h[1], (int)l[1]);
+        }
+        return combine(a, b);
+    }
+}
+
+// {sum, sum, max, max, max, sum} over the wavefront, in the order 32, 16, .. 1
+template <int O = 32> __device__ inline void wave_reduce6(double v[6])
+{
+    auto add = [](double a, double b) { return a + b; };
+    auto most = [](double a, double b) { return fmax(a, b); };
+    v[0] = xor_combine<O>(v[0], add);
+    v[1] = xor_combine<O>(v[1], add);
+    v[5] = xor_combine<O>(v[5], add);
+    v[2] = xor_combine<O>(v[2], most);
+    v[3] = xor_combine<O>(v[3], most);
+    v[4] = xor_combine<O>(v[4], most);
+    if constexpr (O > 1) wave_reduce6<O / 2>(v);
+}
+
+// sum over the LPP lanes of a particle, in the order LPP/2, .. 1
+template <int LPP, typename T> __device__ inline void lane_sum(T &v)
+{
+    if constexpr (LPP > 1) {
+        v += xor_lane<LPP / 2>(v);
+        lane_sum<LPP / 2>(v);
+    }
 }
 
 // LPP lanes share one particle: lane `sub` takes neighbour entries sub, sub+LPP,
@@ -631,14 +694,14 @@ __device__ __forceinline__ void pass_tile_at(const PassArgs<T> &A, const SimDev 
         }
     }
     if (LPP > 1) {
-        lane_sum(acc.div, LPP);
-        lane_sum(acc.lap, LPP);
+        lane_sum<LPP>(acc.div);
+        lane_sum<LPP>(acc.lap);
         for (int d = 0; d < DIM; ++d) {
-            lane_sum(acc.grad[d], LPP);
-            lane_sum(acc.vis[d], LPP);
-            if (CONV) lane_sum(acc.conv[d], LPP);
+            lane_sum<LPP>(acc.grad[d]);
+            lane_sum<LPP>(acc.vis[d]);
+            if (CONV) lane_sum<LPP>(acc.conv[d]);
         }
-        if (CONV) lane_sum(acc.padv, LPP);
+        if (CONV) lane_sum<LPP>(acc.padv);
     }
 
     T Dv = 0, R[3] = {0, 0, 0}, vt2 = 0, dw2 = 0;
@@ -719,23 +782,12 @@ __device__ __forceinline__ void pass_tile_at(const PassArgs<T> &A, const SimDev 
     if (MODE == MODE_PSEUDO) {
         // fixed-order block reduction of {sum |D|, sum |Vtilde|, max |D|, max |Vtilde|}
         __shared__ double lds[kMaxBlock / 64][6];
-        double sd = owner ? fabs((double)Dv) : 0.0;
-        double sv = owner ? sqrt((double)vt2) : 0.0;
-        double md = sd, mv = sv, mw = owner ? (double)dw2 : 0.0;
-        double np = owner ? (double)npairs : 0.0;
-        for (int o = 32; o > 0; o >>= 1) {
-            sd += __shfl_xor(sd, o, 64);
-            sv += __shfl_xor(sv, o, 64);
-            np += __shfl_xor(np, o, 64);
-            md = fmax(md, __shfl_xor(md, o, 64));
-            mv = fmax(mv, __shfl_xor(mv, o, 64));
-            mw = fmax(mw, __shfl_xor(mw, o, 64));
-        }
+        const double sd = owner ? fabs((double)Dv) : 0.0, sv = owner ? sqrt((double)vt2) : 0.0;
+        double red[6] = {sd, sv, sd, sv, owner ? (double)dw2 : 0.0, owner ? (double)npairs : 0.0};
+        wave_reduce6(red);
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        if (lane == 0) {
-            lds[wave][0] = sd; lds[wave][1] = sv; lds[wave][2] = md; lds[wave][3] = mv; lds[wave][4] = mw;
-            lds[wave][5] = np;
-        }
+        if (lane == 0)
+            for (int k = 0; k < 6; ++k) lds[wave][k] = red[k];
         __syncthreads();
         if (threadIdx.x == 0) {
             double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0, a5 = 0;
@@ -912,7 +964,9 @@ struct FinArgs {
     SimIter *iters;
     const double4 *partials;
     const double2 *partials2;
-    const int4 *segs;
+    const int4 *segs;  // {sim, first tile, end tile, place among the sim's segments or -1 for an only one}
+    int4 seg0;         // the segment of a context with only one
+    int n_segs;
     double4 *seg_p;
     double2 *seg_p2;
     uint32_t *tickets;
@@ -947,14 +1001,7 @@ __device__ inline uint32_t move_build_flags(const FinArgs &A)
 __device__ inline void fin_block_reduce(double v[6])
 {
     __shared__ double lds[kFinThreads / 64][6];
-    for (int o = 32; o > 0; o >>= 1) {
-        v[0] += __shfl_xor(v[0], o, 64);
-        v[1] += __shfl_xor(v[1], o, 64);
-        v[5] += __shfl_xor(v[5], o, 64);
-        v[2] = fmax(v[2], __shfl_xor(v[2], o, 64));
-        v[3] = fmax(v[3], __shfl_xor(v[3], o, 64));
-        v[4] = fmax(v[4], __shfl_xor(v[4], o, 64));
-    }
+    wave_reduce6(v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0)
         for (int k = 0; k < 6; ++k) lds[wave][k] = v[k];
@@ -1094,19 +1141,10 @@ __device__ inline void close_iteration(SimIter &It, const FinState &F, const dou
 __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
 {
     __shared__ int last;
-    const int4 sg = A.segs[g];
+    const int4 sg = A.n_segs == 1 ? A.seg0 : A.segs[g];
     const int s = sg.x;
     SimIter &It = A.iters[s];
-    if (It.done) {
-        if (sg.w == 0 && threadIdx.x == 0) {
-            A.done_out[s] = 1;
-            if (A.publish) publish_report(A, s, It);
-        }
-        return;
-    }
-    const SimDev &S = A.sims[s];
-    FinState F;
-    if (threadIdx.x == 0) load_fin_state(F, It, S);
+    // every load whose address is known now is issued before the first wait
     double red[6] = {0, 0, 0, 0, 0, 0};
     const int t = sg.y + (int)threadIdx.x;
     if (t < sg.z) {
@@ -1114,7 +1152,35 @@ __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
         const double2 p2 = A.partials2[t];
         red[0] = p.x; red[1] = p.y; red[2] = p.z; red[3] = p.w; red[4] = p2.x; red[5] = p2.y;
     }
+    const SimDev &S = A.sims[s];
+    FinState F;
+    if (threadIdx.x == 0) load_fin_state(F, It, S);
+    if (It.done) {
+        if (sg.w <= 0 && threadIdx.x == 0) {
+            A.done_out[s] = 1;
+            if (A.publish) publish_report(A, s, It);
+        }
+        return;
+    }
     fin_block_reduce(red);
+    if (sg.w < 0) {
+        // a sim of one segment (up to kSegTiles tiles): its sums are the segment's.
+        // The reduction over segments would combine them with +0.0 only, which leaves
+        // a sum s as s + 0.0 and a maximum m as fmax(m, 0.0); its arrival count, the
+        // fences and the second reduction took half of this launch.
+        if (threadIdx.x == 0) {
+            red[0] += 0.0;
+            red[1] += 0.0;
+            red[5] += 0.0;
+            red[2] = fmax(red[2], 0.0);
+            red[3] = fmax(red[3], 0.0);
+            red[4] = fmax(red[4], 0.0);
+            close_iteration(It, F, red);
+            A.done_out[s] = It.done;
+            if (A.publish) publish_report(A, s, It);
+        }
+        return;
+    }
     if (threadIdx.x == 0) {
         A.seg_p[g] = make_double4(red[0], red[1], red[2], red[3]);
         A.seg_p2[g] = make_double2(red[4], red[5]);
@@ -1259,7 +1325,7 @@ FinArgs fin_args(Ctx &c, bool publish)
 {
     FinArgs a;
     a.sims = c.sims; a.iters = c.iters; a.partials = c.partials; a.partials2 = c.partials2;
-    a.segs = c.segs; a.seg_p = c.seg_p; a.seg_p2 = c.seg_p2; a.tickets = c.tickets;
+    a.segs = c.segs; a.seg0 = c.seg0; a.n_segs = c.n_segs; a.seg_p = c.seg_p; a.seg_p2 = c.seg_p2; a.tickets = c.tickets;
     a.done_out = c.done_dev; a.flags = c.flags; a.n_sims = c.n_sims;
     a.h_flags = c.m_flags_d; a.h_reps = c.m_reps_d;
     a.pubcount = c.pubcount;

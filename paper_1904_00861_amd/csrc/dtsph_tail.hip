@@ -74,14 +74,7 @@ template <typename L> __device__ inline void fin_reduce_any(double out[6], int n
         if (w < gn) {  // uniform per wave
             double v[6];
             load(w * 64 + lane, v);
-            for (int o = 32; o > 0; o >>= 1) {
-                v[0] += __shfl_xor(v[0], o, 64);
-                v[1] += __shfl_xor(v[1], o, 64);
-                v[5] += __shfl_xor(v[5], o, 64);
-                v[2] = fmax(v[2], __shfl_xor(v[2], o, 64));
-                v[3] = fmax(v[3], __shfl_xor(v[3], o, 64));
-                v[4] = fmax(v[4], __shfl_xor(v[4], o, 64));
-            }
+            wave_reduce6(v);
             if (lane == 0)
                 for (int k = 0; k < 6; ++k) lds[w][k] = v[k];
         }
