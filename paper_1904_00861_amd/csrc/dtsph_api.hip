@@ -458,10 +458,14 @@ void setup_tiles(Ctx &c)
         for (int off = 0; off < (int)c.nf[s]; off += per) tiles.push_back(make_int2(s, c.fluid_begin[s] + off));
         S.tile_end = (int)tiles.size();
         S.seg_begin = (int)segs.size();
-        for (int t = S.tile_begin, k = 0; t < S.tile_end; t += kSegTiles, ++k)
-            segs.push_back(make_int4(s, t, std::min(t + kSegTiles, S.tile_end), k));
+        if (S.tile_end > S.tile_begin && S.tile_end - S.tile_begin <= kSoloSegs * kSegTiles) {
+            // one workgroup closes the sim
+            segs.push_back(make_int4(s, S.tile_begin, S.tile_end, S.tile_end - S.tile_begin <= kSegTiles ? -1 : -2));
+        } else {
+            for (int t = S.tile_begin, k = 0; t < S.tile_end; t += kSegTiles, ++k)
+                segs.push_back(make_int4(s, t, std::min(t + kSegTiles, S.tile_end), k));
+        }
         S.seg_count = (int)segs.size() - S.seg_begin;
-        if (S.seg_count == 1) segs.back().w = -1;
     }
     c.seg0 = segs.empty() ? make_int4(0, 0, 0, 0) : segs[0];
     c.n_tiles = (int)tiles.size();

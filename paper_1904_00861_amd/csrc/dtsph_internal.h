@@ -33,6 +33,7 @@ constexpr int kMaxCellOccupancy = 4096;
 constexpr int kMaxBlock = 256;
 constexpr int kMaxRanges = 32;       // active tile ranges passed to the pair pass
 constexpr int kSegTiles = 256;       // tiles per residual segment (one finalize workgroup)
+constexpr int kSoloSegs = 4;          // segments that one finalize workgroup takes for a whole sim
 constexpr int kMaxTileRows = 32;     // cell rows per strip of the staged neighbour kernel
 constexpr int kTailMaxSims = 256;    // sims of a context that may use tail launches
 constexpr int64_t kTailSpinDefault = 1LL << 22;  // polls of a tail barrier word before a wait gives up
@@ -52,7 +53,7 @@ struct SimDev {
     int wall_begin;      // first wall (index among the walls: slot Nf + wall_begin)
     int key_base;        // first fluid key; wall keys add the total cell count
     int tile_begin, tile_end;  // fluid tiles of this sim (residual partials)
-    int seg_begin, seg_count;  // residual segments (runs of up to kSegTiles tiles)
+    int seg_begin, seg_count;  // residual segments (runs of up to kSegTiles tiles; one for a sim of up to kSoloSegs)
     int ncell[3];
     int cell_div;        // cells of side >= (kappa h + skin) / cell_div; blocks of +-cell_div cells
     int tile_w, tile_h;  // cells per strip of the staged neighbour kernel (2D)

@@ -421,8 +421,8 @@ void launch_wall(Ctx &c, int mode, bool cand_lists)
     if (c.Nw == 0) return;
     const WallArgs<T> a = wall_args<T>(c, mode, cand_lists);
     int t0 = mode == MODE_PSEUDO ? timer_begin(c, 1) : -1;
-    if (c.max_dim == 2) DTSPH_LAUNCH(c, (k_wall<T, 2>), dim3(grid_for(c.Nw)), dim3(256), 0, c.stream, a);
-    else DTSPH_LAUNCH(c, (k_wall<T, 3>), dim3(grid_for(c.Nw)), dim3(256), 0, c.stream, a);
+    if (c.max_dim == 2) DTSPH_LAUNCH(c, (k_wall<T, 2>), dim3(grid_for(4 * c.Nw)), dim3(256), 0, c.stream, a);
+    else DTSPH_LAUNCH(c, (k_wall<T, 3>), dim3(grid_for(4 * c.Nw)), dim3(256), 0, c.stream, a);
     DTSPH_HIP_CHECK(hipGetLastError());
     if (mode == MODE_PSEUDO) timer_end(c, t0, 1);
 }
@@ -452,7 +452,7 @@ void launch_finalize_wall(Ctx &c, bool publish, int next)
 {
     const FinArgs f = fin_args(c, publish);
     const WallArgs<T> w = wall_args<T>(c, MODE_PSEUDO, false);
-    const dim3 grid(c.n_segs + ceil_div(c.Nw, kFinThreads));
+    const dim3 grid(c.n_segs + ceil_div(4 * c.Nw, kFinThreads));
     if (c.max_dim == 2) DTSPH_LAUNCH(c, (k_finalize_wall<T, 2>), grid, dim3(kFinThreads), 0, c.stream, f, w, c.n_segs, next);
     else DTSPH_LAUNCH(c, (k_finalize_wall<T, 3>), grid, dim3(kFinThreads), 0, c.stream, f, w, c.n_segs, next);
     DTSPH_HIP_CHECK(hipGetLastError());

@@ -852,11 +852,46 @@ template <typename T> struct WallArgs {
     double *x_alt;   // MODE_PRE: walls keep their position
 };
 
+// x of lane L of the quad, in all four lanes
+template <int L> __device__ inline float quad_lane(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), L * 0x55, 0xf, 0xf, true));
+}
+template <int L> __device__ inline double quad_lane(double x)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), L * 0x55, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), L * 0x55, 0xf, 0xf, true));
+}
+
+// Sums of the wall pass: of W, p W, rho r W and V W over the fluid neighbours.
+template <typename T> struct WallSums {
+    T S0 = 0, Sp = 0, Srr[3] = {0, 0, 0}, Sv[3] = {0, 0, 0};
+};
+
+// One neighbour's terms from the quad's lane L (zeros for a slot past the list,
+// which leave every sum as it is).
+template <int L, int DIM, typename T>
+__device__ inline void wall_add(WallSums<T> &a, T W, T p, const T rr[3], const T v[3])
+{
+    const T w = quad_lane<L>(W);
+    a.S0 += w;
+    a.Sp = mad(quad_lane<L>(p), w, a.Sp);
+    for (int d = 0; d < DIM; ++d) {
+        a.Srr[d] = mad(quad_lane<L>(rr[d]), w, a.Srr[d]);
+        a.Sv[d] = mad(quad_lane<L>(v[d]), w, a.Sv[d]);
+    }
+}
+
 // Wall particle iw of sim S from the fluid records of buffer `par` (position
 // records of buffer `ppar` for moving sims): its record (ghost velocity and
 // pressure) into the same buffer and, with write_pw, the wall-pressure array.
+// Called by the four lanes of a quad, sub = 0 .. 3: each gathers and evaluates
+// every fourth neighbour, and all four add the terms up in list order. The launch is
+// a chain of dependent loads (few walls, up to 20 fluid neighbours each): one thread
+// per wall took two round trips for every 8 neighbours, the quad two in all for
+// up to 4 U.
 template <typename T, int DIM>
-__device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev &S, int iw, int par, int ppar,
+__device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev &S, int iw, int sub, int par, int ppar,
                                               bool write_pw)
 {
     using Q = typename V4<T>::type;
@@ -872,18 +907,15 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
     const uint32_t cn = A.cnt[i];
     const int nfl = (int)(cn & 0xffffu);
     const int *__restrict__ nb = A.nbr + i;
-    T S0 = 0, Sp = 0, Srr[3] = {0, 0, 0}, Sv[3] = {0, 0, 0};
-    // fluid neighbours U at a time: U index loads, then 2U record gathers in
-    // flight (slots past the count gather the particle's own records and are
-    // skipped), then the sums in entry order
-    constexpr int U = sizeof(T) == 4 ? 8 : 4;
-    for (int k0 = 0; k0 < nfl; k0 += U) {
+    WallSums<T> acc;
+    constexpr int U = sizeof(T) == 4 ? 6 : 4;
+    for (int k0 = 0; k0 < nfl; k0 += 4 * U) {
         bool ok[U];
         int jj[U];
 #pragma unroll
         for (int m = 0; m < U; ++m) {
-            ok[m] = k0 + m < nfl;
-            jj[m] = ok[m] ? nb[(size_t)(k0 + m) * N] : i;
+            ok[m] = k0 + 4 * m + sub < nfl;
+            jj[m] = ok[m] ? nb[(size_t)(k0 + 4 * m + sub) * N] : i;
         }
         Rec rj[U];
         Q vj[U];
@@ -894,7 +926,7 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
         }
 #pragma unroll
         for (int m = 0; m < U; ++m) {
-            if (!ok[m]) continue;
+            if (k0 + 4 * m >= nfl) continue;  // the same for the whole quad
             T r[3];
             pos.delta(ri, rj[m], r);
             T r2 = mad(r[0], r[0], r[1] * r[1]);
@@ -905,15 +937,22 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
             t2 = t2 > T(0) ? t2 : T(0);
             t1 = t1 > T(0) ? t1 : T(0);
             const T a5 = t3 * t3 * t3 * t3 * t3, b5 = t2 * t2 * t2 * t2 * t2, c5 = t1 * t1 * t1 * t1 * t1;
-            const T W = mad(T(15), c5, mad(T(-6), b5, a5));  // sigma cancels in the ratios
-            S0 += W;
-            Sp = mad(pres<DIM>(vj[m]), W, Sp);
+            const T W0 = mad(T(15), c5, mad(T(-6), b5, a5));  // sigma cancels in the ratios
+            const T W = ok[m] ? W0 : T(0), p = ok[m] ? pres<DIM>(vj[m]) : T(0);
+            T rw[3] = {0, 0, 0}, v[3] = {0, 0, 0};
             for (int d = 0; d < DIM; ++d) {
-                Srr[d] = mad(rho * r[d], W, Srr[d]);
-                Sv[d] = mad(comp(vj[m], d), W, Sv[d]);
+                rw[d] = ok[m] ? rho * r[d] : T(0);
+                v[d] = ok[m] ? comp(vj[m], d) : T(0);
             }
+            wall_add<0, DIM>(acc, W, p, rw, v);
+            wall_add<1, DIM>(acc, W, p, rw, v);
+            wall_add<2, DIM>(acc, W, p, rw, v);
+            wall_add<3, DIM>(acc, W, p, rw, v);
         }
     }
+    if (sub != 0) return;
+    const T S0 = acc.S0, Sp = acc.Sp;
+    const T(&Srr)[3] = acc.Srr, (&Sv)[3] = acc.Sv;
     T vw[3] = {0, 0, 0}, ghost[3] = {0, 0, 0};
     for (int d = 0; d < DIM; ++d) vw[d] = A.vwall[d * A.Nw + iw];
     T pw = 0;
@@ -933,7 +972,7 @@ __device__ __forceinline__ void wall_particle(const WallArgs<T> &A, const SimDev
 template <typename T, int DIM>
 __global__ void __launch_bounds__(256) k_wall(WallArgs<T> A)
 {
-    const int iw = blockIdx.x * blockDim.x + threadIdx.x;
+    const int iw = (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 2, sub = (int)threadIdx.x & 3;
     if (iw >= A.Nw) return;
     if (A.gated && !spec_gate(A.n_sims, A.iters, A.sims)) return;
     const int i = A.Nf + iw;
@@ -942,14 +981,14 @@ __global__ void __launch_bounds__(256) k_wall(WallArgs<T> A)
     const SimDev &S = A.sims[s];
     int par = A.cur, ppar = 0;
     if (A.mode == MODE_PRE) {
-        for (int d = 0; d < 3; ++d) A.x_alt[d * N + i] = A.x[d * N + i];
+        if (sub < 3) A.x_alt[sub * N + i] = A.x[sub * N + i];
     } else {
         const SimIter &It = A.iters[s];
         if (It.done) return;
         par = (A.cur + It.iters) & 1;
         ppar = S.move ? It.iters & 1 : 0;  // moving fluid: records at r^{k+1/2}
     }
-    wall_particle<T, DIM>(A, S, iw, par, ppar, true);
+    wall_particle<T, DIM>(A, S, iw, sub, par, ppar, true);
 }
 
 // ---- residual reduction and stop test (section 3.4) --------------------------
@@ -964,7 +1003,8 @@ struct FinArgs {
     SimIter *iters;
     const double4 *partials;
     const double2 *partials2;
-    const int4 *segs;  // {sim, first tile, end tile, place among the sim's segments or -1 for an only one}
+    const int4 *segs;  // {sim, first tile, end tile, place among the sim's segments; -1: an only one,
+                       // -2: 2 .. kSoloSegs of them in one record}
     int4 seg0;         // the segment of a context with only one
     int n_segs;
     double4 *seg_p;
@@ -1136,12 +1176,77 @@ __device__ inline void close_iteration(SimIter &It, const FinState &F, const dou
     }
 }
 
+// A sim of 2 .. kSoloSegs segments: one workgroup reduces them all and closes the
+// iteration (two segments: 5.3 -> 4.2 us against an arrival count with its fences
+// and a second reduction). The segments' sums are combined as the reduction over
+// the segments in finalize_segment combines them: by butterflies over four values,
+// and with +0.0 or fmax(., 0.0) for the values that are not there.
+__device__ __forceinline__ void finalize_few(const FinArgs &A, int4 sg)
+{
+    const int s = sg.x;
+    SimIter &It = A.iters[s];
+    double v[kSoloSegs][6];
+#pragma unroll
+    for (int j = 0; j < kSoloSegs; ++j) {
+        const int t = sg.y + j * kSegTiles + (int)threadIdx.x;
+        for (int k = 0; k < 6; ++k) v[j][k] = 0.0;
+        if (t < sg.z) {
+            const double4 p = A.partials[t];
+            const double2 p2 = A.partials2[t];
+            v[j][0] = p.x; v[j][1] = p.y; v[j][2] = p.z; v[j][3] = p.w; v[j][4] = p2.x; v[j][5] = p2.y;
+        }
+    }
+    const SimDev &S = A.sims[s];
+    FinState F;
+    if (threadIdx.x == 0) load_fin_state(F, It, S);
+    if (It.done) {
+        if (threadIdx.x == 0) {
+            A.done_out[s] = 1;
+            if (A.publish) publish_report(A, s, It);
+        }
+        return;
+    }
+    __shared__ double seg[kSoloSegs][kFinThreads / 64][6];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nseg = (sg.z - sg.y + kSegTiles - 1) / kSegTiles;
+#pragma unroll
+    for (int j = 0; j < kSoloSegs; ++j)
+        if (j < nseg) {
+            wave_reduce6(v[j]);
+            if (lane == 0)
+                for (int k = 0; k < 6; ++k) seg[j][wave][k] = v[j][k];
+        }
+    __syncthreads();
+    if (wave != 0) return;
+    const int k = lane < 6 ? lane : 0;  // lane k: value k
+    const bool sum = k < 2 || k == 5;
+    double u[kSoloSegs] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < kSoloSegs; ++j)
+        if (j < nseg) {
+            u[j] = seg[j][0][k];
+            for (int w = 1; w < kFinThreads / 64; ++w)
+                u[j] = sum ? u[j] + seg[j][w][k] : fmax(u[j], seg[j][w][k]);
+        }
+    const double all = sum ? (u[0] + u[2]) + (u[1] + u[3]) + 0.0
+                           : fmax(fmax(fmax(u[0], u[2]), fmax(u[1], u[3])), 0.0);
+    double red[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+        red[q] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(all), q),
+                                  __builtin_amdgcn_readlane(__double2loint(all), q));
+    if (lane != 0) return;
+    close_iteration(It, F, red);
+    A.done_out[s] = It.done;
+    if (A.publish) publish_report(A, s, It);
+}
+
 // Segment g of the residual reduction; the last segment of a sim to arrive
 // closes the sim's iteration (stop test, report).
 __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
 {
     __shared__ int last;
     const int4 sg = A.n_segs == 1 ? A.seg0 : A.segs[g];
+    if (sg.w < -1) return finalize_few(A, sg);
     const int s = sg.x;
     SimIter &It = A.iters[s];
     // every load whose address is known now is issued before the first wait
@@ -1226,12 +1331,12 @@ __global__ void __launch_bounds__(kFinThreads) k_finalize_wall(FinArgs F, WallAr
         finalize_segment(F, blockIdx.x);
         return;
     }
-    const int iw = ((int)blockIdx.x - n_segs) * kFinThreads + (int)threadIdx.x;
+    const int iw = (((int)blockIdx.x - n_segs) * kFinThreads + (int)threadIdx.x) >> 2, sub = (int)threadIdx.x & 3;
     if (iw >= W.Nw) return;
     const int s = W.simid[W.Nf + iw];
     if (W.iters[s].done) return;  // stopped before iteration k (or just now: either way unused)
     const SimDev &S = W.sims[s];
-    wall_particle<T, DIM>(W, S, iw, (W.cur + next) & 1, S.move ? next & 1 : 0, false);
+    wall_particle<T, DIM>(W, S, iw, sub, (W.cur + next) & 1, S.move ? next & 1 : 0, false);
 }
 
 // End of a loop whose wall passes ran with the residual reductions: each wall

@@ -266,9 +266,9 @@ k_tail(PassArgs<T> A, FinArgs F, WallArgs<T> W, TailArgs L)
         prefetch_partials(pre, S, L.part4[q], L.part2[q]);
         const int stop = tail_close(F, s, S, It, pre, L.part4[q], L.part2[q], bi == 0);
         if (walls) {  // the sim's walls for iteration k + 1 (records of its fluid at k + 1)
-            const int end = S.wall_begin + S.nw, stride = nt * (int)blockDim.x;
-            for (int iw = S.wall_begin + bi * (int)blockDim.x + (int)threadIdx.x; iw < end; iw += stride)
-                wall_particle<T, DIM>(W, S, iw, (W.cur + k + 1) & 1, 0, false);
+            const int end = S.wall_begin + S.nw, per = (int)blockDim.x >> 2, stride = nt * per;
+            for (int iw = S.wall_begin + bi * per + ((int)threadIdx.x >> 2); iw < end; iw += stride)
+                wall_particle<T, DIM>(W, S, iw, (int)threadIdx.x & 3, (W.cur + k + 1) & 1, 0, false);
             if (stop) return;
             if (!sim_meet(L, seat, phase)) return;
         } else if (stop) {
