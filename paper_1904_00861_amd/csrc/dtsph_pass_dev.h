@@ -1286,20 +1286,28 @@ __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
         }
         return;
     }
+    // The segment sums are written through with agent-scope stores and read back with
+    // agent-scope loads, and the arrival is counted once the stores have completed, so
+    // neither side needs an agent fence (an L2 write-back, an L2 invalidation): 518k
+    // particles with walls 8.7 -> 7.3 us, 160k 7.2 -> 6.5.
     if (threadIdx.x == 0) {
-        A.seg_p[g] = make_double4(red[0], red[1], red[2], red[3]);
-        A.seg_p2[g] = make_double2(red[4], red[5]);
-        __threadfence();  // segment sums visible before the arrival is counted
-        last = atomicAdd(&A.tickets[s], 1u) == (uint32_t)(S.seg_count - 1);
+        double *p = (double *)(A.seg_p + g), *p2 = (double *)(A.seg_p2 + g);
+        for (int k = 0; k < 4; ++k) __hip_atomic_store(p + k, red[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int k = 0; k < 2; ++k) __hip_atomic_store(p2 + k, red[4 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        last = __hip_atomic_fetch_add(&A.tickets[s], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+               (uint32_t)(S.seg_count - 1);
     }
     __syncthreads();
     if (!last) return;
-    __threadfence();
     for (int k = 0; k < 6; ++k) red[k] = 0.0;
     const int seg_begin = S.seg_begin, seg_count = S.seg_count;
     for (int q = (int)threadIdx.x; q < seg_count; q += kFinThreads) {
-        const double4 p = A.seg_p[seg_begin + q];
-        const double2 p2 = A.seg_p2[seg_begin + q];
+        auto at = [](const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        const double *s4 = (const double *)(A.seg_p + seg_begin + q), *s2 = (const double *)(A.seg_p2 + seg_begin + q);
+        const double4 p = make_double4(at(s4), at(s4 + 1), at(s4 + 2), at(s4 + 3));
+        const double2 p2 = make_double2(at(s2), at(s2 + 1));
         if (q == (int)threadIdx.x) {
             red[0] = p.x; red[1] = p.y; red[2] = p.z; red[3] = p.w; red[4] = p2.x; red[5] = p2.y;
         } else {
