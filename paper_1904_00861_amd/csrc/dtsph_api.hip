@@ -625,6 +625,18 @@ void readback_flags(Ctx &c)
     check_host_flags(c);
 }
 
+// Build flags that have come with a loop's reports. An error ends the loop: the
+// launches still in flight (the second group of launch_window) are waited for first
+// and the flags they raise moved too, so that none is left for a later call to find
+// on a state set since.
+void check_loop_flags(Ctx &c)
+{
+    const volatile int *f = c.flags_host;
+    bool any = false;
+    for (int k = 0; k < F_COUNT; ++k) any = any || f[k];
+    if (any) readback_flags(c);
+}
+
 // Exact neighbour lists for the current positions: a filter of the candidate
 // lists when every particle is known to be within skin/2 of where the lists
 // were built, else a full cell build.
@@ -882,7 +894,8 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
 {
     for (;;) {
         wait_reports(c, L.window ? L.mark_seq[0] : c.seq);  // k_finalize wrote the mapped reports
-        check_host_flags(c);
+        if (c.timing) resolve_timers(c);
+        check_loop_flags(c);
         if (L.window) {
             L.known = L.mark_it[0];
             L.mark_seq[0] = L.mark_seq[1];
