@@ -105,15 +105,22 @@ size_t workspace_need(const Ctx &c)
     return total;
 }
 
-// Move every device array to `base` (a caller workspace of workspace_need(c)
-// bytes) or, with base == nullptr, to fresh library allocations; contents are
-// copied on the context's stream, old library allocations freed.
 void clear_graphs(Ctx &c)
 {
     for (auto &kv : c.graph_cache) (void)hipGraphExecDestroy(kv.second);
     c.graph_cache.clear();
 }
 
+// The arrays behind the build flags in the allocation of c.flags.
+void flag_views(Ctx &c)
+{
+    c.done_dev = c.flags + F_COUNT;
+    c.moved_dev = (uint32_t *)(c.done_dev + c.n_sims);
+}
+
+// Move every device array to `base` (a caller workspace of workspace_need(c)
+// bytes) or, with base == nullptr, to fresh library allocations; contents are
+// copied on the context's stream, old library allocations freed.
 void relocate(Ctx &c, char *base, size_t size)
 {
     clear_graphs(c);  // they hold the old addresses
@@ -142,7 +149,7 @@ void relocate(Ctx &c, char *base, size_t size)
     for (void *p : c.owned) (void)hipFree(p);
     c.owned = std::move(fresh_owned);
     for (size_t i = 0; i < c.arrays.size(); ++i) *c.arrays[i].slot = fresh[i];
-    c.done_dev = c.flags + F_COUNT;
+    flag_views(c);
     c.workspace = base;
     c.workspace_size = base ? size : 0;
 }
@@ -557,24 +564,17 @@ void check_host_flags(Ctx &c)
                                         "box or clumped); particle state is undefined");
 }
 
-// Takes sim s's report from mapped memory if it is complete, is that of the finalize
-// launch with sequence number `want` or a later one, and the build flags it names
-// have arrived.
+// Takes sim s's report of the finalize launch with sequence number `want` or a later
+// one from mapped memory, if it is there (accept_report).
 bool take_report(Ctx &c, int s, int want)
 {
-    const volatile uint32_t *src = (const volatile uint32_t *)(c.mirror_reps + s);
-    if ((int)(src[14] - (uint32_t)want) < 0) return false;
     MirrorRep r;
-    uint32_t w[16];
-    for (int k = 0; k < 16; ++k) w[k] = src[k];
-    if (w[15] != report_check(w) || (int)(w[14] - (uint32_t)want) < 0) return false;
-    std::memcpy(&r, w, sizeof r);
-    for (int k = 0; k < F_COUNT; ++k)
-        if (((r.state >> (16 + k)) & 1u) && !((const volatile int *)c.flags_host)[k]) return false;
+    if (!accept_report((const volatile uint32_t *)(c.mirror_reps + s), c.flags_host, want, r)) return false;
     HostRep &h = c.reps_host[s];
     h.iters = r.iters;
     h.reason = (int)(r.state & 255u);
     h.done = (int)((r.state >> 8) & 1u);
+    h.moved = r.state >> 16;
     h.rp_mean = r.rp_mean;
     h.rv_mean = r.rv_mean;
     h.rp_max = r.rp_max;
@@ -625,16 +625,13 @@ void readback_flags(Ctx &c)
     check_host_flags(c);
 }
 
-// Build flags that have come with a loop's reports. An error ends the loop: the
+// Build flags named in a loop's reports. An error ends the loop: the
 // launches still in flight (the second group of launch_window) are waited for first
 // and the flags they raise moved too, so that none is left for a later call to find
 // on a state set since.
 void check_loop_flags(Ctx &c)
 {
-    const volatile int *f = c.flags_host;
-    bool any = false;
-    for (int k = 0; k < F_COUNT; ++k) any = any || f[k];
-    if (any) readback_flags(c);
+    if (c.reps_host[0].moved) readback_flags(c);
 }
 
 // Exact neighbour lists for the current positions: a filter of the candidate
@@ -1400,8 +1397,8 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
         dev_alloc(c, c.tickets, sizeof(uint32_t) * n_sims);
         dev_alloc(c, c.pubcount, sizeof(uint32_t) * n_sims);
         dev_alloc(c, c.partials2, sizeof(double2) * max_tiles);
-        dev_alloc(c, c.flags, sizeof(int) * (F_COUNT + n_sims));
-        c.done_dev = c.flags + F_COUNT;
+        dev_alloc(c, c.flags, sizeof(int) * (F_COUNT + n_sims + 1));
+        flag_views(c);
         dev_alloc(c, c.init_slot, sizeof(int) * 2 * (size_t)N);
         if (c.any_shift) {
             dev_alloc(c, c.sh_dr, 8 * 3 * (size_t)Nf);
@@ -1443,7 +1440,7 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
             c.sh_max_d = (double *)(db + 32);
         }
         DTSPH_HIP_CHECK(hipMemcpy(c.init_slot, init_slot.data(), sizeof(int) * 2 * N, hipMemcpyHostToDevice));
-        DTSPH_HIP_CHECK(hipMemset(c.flags, 0, sizeof(int) * (F_COUNT + n_sims)));
+        DTSPH_HIP_CHECK(hipMemset(c.flags, 0, sizeof(int) * (F_COUNT + n_sims + 1)));
         DTSPH_HIP_CHECK(hipMemset(c.tickets, 0, sizeof(uint32_t) * n_sims));
         DTSPH_HIP_CHECK(hipMemset(c.pubcount, 0, sizeof(uint32_t) * n_sims));
         DTSPH_HIP_CHECK(hipMemset(c.cell_start, 0, 4 * (size_t)(2 * c.C_max + 1)));

@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "dtsph.h"
+#include "dtsph_report.h"
 
 namespace dtsph {
 
@@ -41,9 +42,6 @@ constexpr int kTailSimTiles = 128;   // tiles of one sim in a tail launch (its b
 constexpr int kTailGroup = 32;       // workgroups per first-level barrier word of a tail launch
 
 enum PassMode { MODE_PRE = 0, MODE_PSEUDO = 1 };
-
-// Device flag words
-enum Flag { F_NBR_OVERFLOW = 0, F_NBR_NEEDED = 1, F_CELL_OVERFLOW = 2, F_OUTSIDE = 3, F_SKIN = 4, F_COUNT = 5 };
 
 // Per-sim constants (device). Everything the kernels need, precomputed on the
 // host in float64; FP32 kernels convert once per thread.
@@ -99,32 +97,10 @@ struct SimIter {
     long long pairs;  // fluid-row neighbour pairs of the last iteration
 };
 
-// Per-sim report as published to mapped host memory: one 64-byte line that carries
-// its own proof of being complete. Device writes to different lines of host memory
-// can become visible out of order (a fence between them does not prevent it: a
-// separate stop flag was read stale once in about 10^4 loops, which ended the loop
-// there), so the host takes a line only when its check word fits the rest of it.
-struct alignas(64) MirrorRep {
-    double rp_mean, rv_mean, rp_max, rv_max, disp;
-    long long pairs;
-    int iters;
-    uint32_t state;   // bits 0..7 stop reason, 8 stopped, 16.. build flags moved with this report
-    uint32_t seq;     // the sim's count of published reports
-    uint32_t check;   // report_check of the 15 words before it
-};
-static_assert(sizeof(MirrorRep) == 64, "one line");
-
-__host__ __device__ inline uint32_t report_check(const uint32_t w[16])
-{
-    uint32_t h = 0x2545f491u;
-#pragma unroll
-    for (int k = 0; k < 15; ++k) h = (h ^ w[k]) * 0x9e3779b1u + (h >> 15);
-    return h;
-}
-
 // A report as the host has taken it.
 struct HostRep {
     int iters = 0, reason = 0, done = 0;
+    uint32_t moved = 0;  // build flags named in it
     double rp_mean = 0, rv_mean = 0, rp_max = 0, rv_max = 0, disp = 0;
     long long pairs = 0;
 };
@@ -271,8 +247,9 @@ struct Ctx {
     std::vector<double> shift_disp;
     double4 *partials = nullptr;
     double2 *partials2 = nullptr;         // per tile: max |V^{k+1} - V^(0)|^2, pairs
-    int *flags = nullptr;
-    int *done_dev = nullptr;
+    int *flags = nullptr;                 // F_COUNT build flags, then done_dev and moved_dev
+    int *done_dev = nullptr;              // per sim: stop flag
+    uint32_t *moved_dev = nullptr;        // build flags moved to host memory since k_publish
     int *init_slot = nullptr;             // caller index -> slot before any sort
 
     // mapped host memory written by the reports and k_publish (host and device views)

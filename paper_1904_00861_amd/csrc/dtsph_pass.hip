@@ -435,7 +435,7 @@ void launch_gate(Ctx &c)
 
 void launch_publish(Ctx &c)
 {
-    DTSPH_LAUNCH(c, k_publish, dim3(1), dim3(64), 0, c.stream, c.flags, c.m_flags_d);
+    DTSPH_LAUNCH(c, k_publish, dim3(1), dim3(64), 0, c.stream, c.flags, c.moved_dev, c.m_flags_d);
     DTSPH_HIP_CHECK(hipGetLastError());
 }
 

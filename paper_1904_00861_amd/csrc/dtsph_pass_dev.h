@@ -1012,6 +1012,7 @@ struct FinArgs {
     uint32_t *tickets;
     int *done_out, *flags;
     int n_sims;
+    uint32_t *moved;   // build flags moved so far (move_build_flags)
     int *h_flags;
     MirrorRep *h_reps;
     uint32_t *pubcount;
@@ -1019,22 +1020,6 @@ struct FinArgs {
 };
 
 constexpr int kFinThreads = kSegTiles;
-
-// Build flags move to mapped memory with sim 0's report, which names them: the host
-// waits for those. Returns their bits.
-__device__ inline uint32_t move_build_flags(const FinArgs &A)
-{
-    uint32_t moved = 0;
-    for (int k = 0; k < F_COUNT; ++k) {
-        const int f = A.flags[k];
-        if (f) {
-            A.h_flags[k] = f;
-            A.flags[k] = 0;
-            moved |= 1u << k;
-        }
-    }
-    return moved;
-}
 
 // Fixed-order workgroup reduction of {sum, sum, max, max, max, sum}; result in
 // thread 0.
@@ -1075,7 +1060,7 @@ __device__ inline void publish_report(const FinArgs &A, int s, const SimIter &It
     w[10] = (uint32_t)It.pairs;
     w[11] = (uint32_t)((unsigned long long)It.pairs >> 32);
     w[12] = (uint32_t)It.iters;
-    const uint32_t moved = s == 0 ? move_build_flags(A) : 0u;
+    const uint32_t moved = s == 0 ? move_build_flags(A.flags, A.h_flags, A.moved) : 0u;
     w[13] = (uint32_t)It.reason | (It.done ? 256u : 0u) | (moved << 16);
     const uint32_t q = A.pubcount[s] + 1u;  // one publishing thread per sim and launch
     A.pubcount[s] = q;
@@ -1366,10 +1351,12 @@ __global__ void __launch_bounds__(256) k_wall_pressure(int Nw, int Nf, const int
 }
 
 // Move the build flags to mapped host memory, so one stream sync makes them
-// readable without a separate copy.
-__global__ void k_publish(int *__restrict__ flags, int *__restrict__ h_flags)
+// readable without a separate copy. The host reads and clears all of them after
+// that sync: none is named in a report any more.
+__global__ void k_publish(int *__restrict__ flags, uint32_t *__restrict__ moved, int *__restrict__ h_flags)
 {
     const int i = threadIdx.x;
+    if (i == 0) *moved = 0u;
     if (i < F_COUNT && flags[i]) {
         h_flags[i] = flags[i];
         flags[i] = 0;
@@ -1440,7 +1427,7 @@ FinArgs fin_args(Ctx &c, bool publish)
     a.sims = c.sims; a.iters = c.iters; a.partials = c.partials; a.partials2 = c.partials2;
     a.segs = c.segs; a.seg0 = c.seg0; a.n_segs = c.n_segs; a.seg_p = c.seg_p; a.seg_p2 = c.seg_p2; a.tickets = c.tickets;
     a.done_out = c.done_dev; a.flags = c.flags; a.n_sims = c.n_sims;
-    a.h_flags = c.m_flags_d; a.h_reps = c.m_reps_d;
+    a.moved = c.moved_dev; a.h_flags = c.m_flags_d; a.h_reps = c.m_reps_d;
     a.pubcount = c.pubcount;
     a.publish = publish ? 1 : 0;
     if (publish) ++c.seq;  // every sim's count advances once per publishing launch
