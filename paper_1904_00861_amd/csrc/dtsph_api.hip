@@ -715,6 +715,23 @@ void shift_outcome(Ctx &c, bool ok)
     c.shift_nosync = c.shift_miss >= 3;
 }
 
+// Largest shift of launch `want` (c.shift_seq: the last one), which a later launch's
+// report or a stream sync has shown to be over: its line can still be on its way.
+double largest_shift(Ctx &c, int want)
+{
+    double mx;
+    for (long spins = 1, after = 0; !accept_shift((const volatile uint32_t *)c.sh_max_h, want, mx); ++spins) {
+        __builtin_ia32_pause();
+        if ((spins & 1023) != 0) continue;
+        const hipError_t e = hipStreamQuery(c.stream);
+        if (e == hipSuccess && ++after >= 1000)
+            throw ApiError(DTSPH_EHIP, "the shift's launches completed without publishing the largest shift");
+        if (e != hipSuccess && e != hipErrorNotReady) throw HipError(e, "hipStreamQuery", __FILE__, __LINE__);
+    }
+    c.tstats.last_max_shift = mx;
+    return mx;
+}
+
 // After the shift kernels: the next rate pass may run on the candidate lists
 // only if they cover the shifted positions, which needs the largest shift read
 // back (a stream sync). After three steps in a row whose shifts left the skin,
@@ -726,12 +743,12 @@ void shift_decision(Ctx &c, bool use_cand)
         c.cand_ok = false;
         c.shift_pending = true;
         c.shift_pending_cand = use_cand;
+        c.shift_pending_seq = c.shift_seq;
         c.shift_disp = c.last_disp;
     } else {
         DTSPH_HIP_CHECK(hipStreamSynchronize(c.stream));
         mirror_pull(c);
-        const double mx = *(volatile double *)c.sh_max_h;
-        c.tstats.last_max_shift = mx;
+        const double mx = largest_shift(c, c.shift_seq);
         c.cand_ok = shift_cand_ok(c, mx, use_cand, c.last_disp);
         shift_outcome(c, c.cand_ok);
     }
@@ -901,8 +918,7 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
         }
         if (c.shift_pending) {  // the last shift has finished: book its size
             c.shift_pending = false;
-            const double mx = *(volatile double *)c.sh_max_h;
-            c.tstats.last_max_shift = mx;
+            const double mx = largest_shift(c, c.shift_pending_seq);
             shift_outcome(c, shift_cand_ok(c, mx, c.shift_pending_cand, c.shift_disp));
         }
         bool all = true;
@@ -1436,8 +1452,8 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
             c.mirror_reps = (MirrorRep *)(hb + 64);
             c.m_flags_d = (int *)db;
             c.m_reps_d = (MirrorRep *)(db + 64);
-            c.sh_max_h = (double *)(hb + 32);
-            c.sh_max_d = (double *)(db + 32);
+            c.sh_max_h = (ShiftRep *)(hb + 32);
+            c.sh_max_d = (ShiftRep *)(db + 32);
         }
         DTSPH_HIP_CHECK(hipMemcpy(c.init_slot, init_slot.data(), sizeof(int) * 2 * N, hipMemcpyHostToDevice));
         DTSPH_HIP_CHECK(hipMemset(c.flags, 0, sizeof(int) * (F_COUNT + n_sims + 1)));

@@ -244,6 +244,7 @@ struct Ctx {
     // leaving the candidate skin (checked later, at the next wait)
     int shift_miss = 0;
     bool shift_nosync = false, shift_pending = false, shift_pending_cand = false;
+    int shift_seq = 0, shift_pending_seq = 0;  // last shift launched; the one to be checked
     std::vector<double> shift_disp;
     double4 *partials = nullptr;
     double2 *partials2 = nullptr;         // per tile: max |V^{k+1} - V^(0)|^2, pairs
@@ -288,7 +289,7 @@ struct Ctx {
     double *sh_dr = nullptr, *sh_dp = nullptr;
     void *sh_dv = nullptr;
     double *sh_part = nullptr;
-    double *sh_max_h = nullptr, *sh_max_d = nullptr;  // mapped host memory
+    ShiftRep *sh_max_h = nullptr, *sh_max_d = nullptr;  // mapped host memory
     std::vector<double> last_disp;    // per sim: max |r^{n+1} - r^(0)| of the last loop
 
     std::string err;

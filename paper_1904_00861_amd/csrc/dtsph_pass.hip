@@ -299,8 +299,8 @@ __global__ void __launch_bounds__(256) k_shift_apply(ShiftArgs<T> A)
 }
 
 // Largest shift of the launch into mapped memory (one workgroup).
-__global__ void __launch_bounds__(256) k_shift_max(const double *__restrict__ part, int n, double *out, int gated,
-                                                   int n_sims, const SimIter *__restrict__ iters,
+__global__ void __launch_bounds__(256) k_shift_max(const double *__restrict__ part, int n, ShiftRep *out,
+                                                   uint32_t seq, int gated, int n_sims, const SimIter *__restrict__ iters,
                                                    const SimDev *__restrict__ sims)
 {
     if (gated && !spec_gate(n_sims, iters, sims)) return;
@@ -310,7 +310,11 @@ __global__ void __launch_bounds__(256) k_shift_max(const double *__restrict__ pa
     for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) out[0] = sqrt(fmax(fmax(lds[0], lds[1]), fmax(lds[2], lds[3])));
+    if (threadIdx.x == 0) {
+        uint32_t w[4];
+        shift_words(w, sqrt(fmax(fmax(lds[0], lds[1]), fmax(lds[2], lds[3]))), seq);
+        *(uint4 *)out = make_uint4(w[0], w[1], w[2], w[3]);
+    }
 }
 
 template <typename T>
@@ -571,8 +575,8 @@ void launch_shift(Ctx &c, bool cand_lists)
         DTSPH_LAUNCH(c, (k_shift_sums<T, 3, 4>), dim3(nsum), dim3(256), 0, c.stream, a);
         DTSPH_LAUNCH(c, (k_shift_apply<T, 3>), dim3(nblk), dim3(256), 0, c.stream, a);
     }
-    DTSPH_LAUNCH(c, k_shift_max, dim3(1), dim3(256), 0, c.stream, c.sh_part, nsum, c.sh_max_d, c.gated ? 1 : 0,
-                 c.n_sims, c.iters, c.sims);
+    DTSPH_LAUNCH(c, k_shift_max, dim3(1), dim3(256), 0, c.stream, c.sh_part, nsum, c.sh_max_d,
+                 (uint32_t)++c.shift_seq, c.gated ? 1 : 0, c.n_sims, c.iters, c.sims);
     DTSPH_HIP_CHECK(hipGetLastError());
 }
 

@@ -73,4 +73,35 @@ inline bool accept_report(const volatile uint32_t *line, const volatile int *fla
     return true;
 }
 
+// The largest particle shift of a step: a line of its own, with the number of its
+// launch.
+struct alignas(16) ShiftRep {
+    double most;
+    uint32_t seq, check;
+};
+
+DTSPH_BOTH inline void shift_words(uint32_t w[4], double most, uint32_t seq)
+{
+    uint64_t b;
+    memcpy(&b, &most, 8);
+    w[0] = (uint32_t)b;
+    w[1] = (uint32_t)(b >> 32);
+    w[2] = seq;
+    w[3] = ((w[0] * 0x9e3779b1u ^ w[1]) * 0x85ebca77u ^ seq) * 0xc2b2ae3du + 0x2545f491u;
+}
+
+// Takes the largest shift in `line` if it is complete and that of launch `want` or a
+// later one.
+inline bool accept_shift(const volatile uint32_t *line, int want, double &most)
+{
+    uint32_t w[4], full[4];
+    for (int k = 0; k < 4; ++k) w[k] = line[k];
+    double m;
+    memcpy(&m, w, 8);
+    shift_words(full, m, w[2]);
+    if (w[3] != full[3] || (int)(w[2] - (uint32_t)want) < 0) return false;
+    most = m;
+    return true;
+}
+
 }  // namespace dtsph

@@ -2,7 +2,7 @@
 driver plays the device, whose writes to different lines arrive in any order. A
 report is taken only when it is whole and not older than the one waited for, and
 an error flag moved with an earlier report of the same loop is waited for also
-when only a later report is seen."""
+when only a later report is seen. The largest shift of a step has the same proof."""
 import os
 import shutil
 import subprocess
@@ -105,6 +105,21 @@ int main()
         d.publish(1, false);
         h.line_arrives(d);
         EXPECT(h.take((int)0x80000000u, r) && h.take(0x7fffffff, r) && !h.take((int)0x80000001u, r));
+    }
+    {   // the largest shift: whole, and not an earlier launch's
+        uint32_t line[4] = {}, w[4];
+        double m = -1;
+        EXPECT(!accept_shift(line, 1, m));
+        shift_words(w, 0.0, 1);
+        for (int k = 0; k < 4; ++k) line[k] = w[k];
+        EXPECT(accept_shift(line, 1, m) && m == 0.0 && !accept_shift(line, 2, m));
+        shift_words(w, 0.75, 2);
+        for (int half = 0; half < 2; ++half) {
+            uint32_t torn[4] = {line[0], line[1], line[2], line[3]};
+            for (int k = 0; k < 2; ++k) torn[2 * half + k] = w[2 * half + k];
+            EXPECT(!accept_shift(torn, 1, m) && !accept_shift(torn, 2, m));
+        }
+        EXPECT(accept_shift(w, 2, m) && m == 0.75 && accept_shift(w, 1, m));
     }
     printf(fails ? "%d checks failed\n" : "all checks passed\n", fails);
     return fails != 0;
