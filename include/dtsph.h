@@ -380,9 +380,12 @@ int dtsph_neighbor_list(dtsph_ctx *ctx, int32_t sim, int64_t *offsets, int32_t *
                                   in {1, 2, 3} (default 2); the search visits
                                   +-value cells per axis                      */
 #define DTSPH_OPT_NBR_LANES 9  /* lanes per particle of the neighbour-list
-                                  build: 1, 2, 4, 8 (0: automatic, which may
-                                  also take one wavefront per cell; the lists
-                                  and their order are the same)              */
+                                  build: 1, 2, 4, 8, or 64 for one wavefront
+                                  per cell (0: automatic, any of them); the
+                                  lists and their order are the same. With 64,
+                                  sims with a periodic axis of fewer than
+                                  2 * cell subdivision + 3 cells take 8 lanes
+                                  per particle                               */
 #define DTSPH_OPT_GRAPHS 10    /* 1: dtsph_step records the segment from the
                                   rate pass to the first chunk of pseudo-
                                   iterations as a HIP graph (one per launch

@@ -1749,8 +1749,8 @@ int dtsph_set_option(dtsph_ctx *ctx, int32_t option, int64_t value)
             c.graphs = value != 0;
             break;
         case DTSPH_OPT_NBR_LANES:
-            if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8)
-                throw ApiError(DTSPH_EINVAL, "neighbour-build lanes must be 0, 1, 2, 4 or 8");
+            if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8 && value != kNbrCell)
+                throw ApiError(DTSPH_EINVAL, "neighbour-build lanes must be 0, 1, 2, 4, 8 or 64 (a wavefront per cell)");
             c.g_nbr = (int)value;
             break;
         case DTSPH_OPT_ABS32_POSITIONS: {
@@ -1837,9 +1837,9 @@ int dtsph_autotune(dtsph_ctx *ctx, int32_t repeats, dtsph_tune_report *out)
             for (int m = 1; m <= 3; ++m) {
                 setup_keys(c, m);
                 DTSPH_HIP_CHECK(hipMemcpy(c.sims, c.sims_h.data(), sizeof(SimDev) * c.n_sims, hipMemcpyHostToDevice));
-                // g = 0: the staged-tile kernel (where it applies), 64: a wavefront per
+                // g = 0: the staged-tile kernel (where it applies), kNbrCell: a wavefront per
                 // cell, else lanes per particle
-                for (int g : {0, 1, 2, 4, 8, 64}) {
+                for (int g : {0, 1, 2, 4, 8, kNbrCell}) {
                     if (g == 0 && c.n_strips == 0) continue;
                     c.nbr_tiles = g == 0 ? 1 : 0;
                     if (g > 0) c.g_nbr = g;

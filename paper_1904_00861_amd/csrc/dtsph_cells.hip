@@ -1252,7 +1252,7 @@ template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a,
     }
 }
 
-// Neighbour kernel of a context that was not tuned: one wavefront per cell (64) in 3D
+// Neighbour kernel of a context that was not tuned: one wavefront per cell (kNbrCell) in 3D
 // (full builds of 262k particles, FP32: 414 us against 453 with 2 lanes per particle, the
 // best lane count; 104k, FP64: 204 against 292) and in 2D up to 20k particles (2.5k: 33
 // against 40 us with 8 lanes; 11.6k: 42 against 48; 25k: 50 both; 160k: 134 against 88 with 2
@@ -1261,7 +1261,7 @@ template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a,
 // lanes 88, 4 lanes 98; 300k: 2 lanes 181, 1 lane 190; 2.6M: 1 lane).
 int nbr_lanes_for(const Ctx &c)
 {
-    if ((c.max_dim == 3 || c.N < 20000) && c.C <= c.N) return 64;
+    if ((c.max_dim == 3 || c.N < 20000) && c.C <= c.N) return kNbrCell;
     return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 ? 2 : 1;
 }
 
@@ -1277,7 +1277,7 @@ template <typename T> void launch_grouped(Ctx &c, const NbrArgs<T> &a, bool filt
     }
     int g = filter ? c.g_filter : c.g_nbr;
     if (!filter && g <= 0) g = nbr_lanes_for(c);
-    if (g == 64) {
+    if (g == kNbrCell) {
         const int blocks = 8 * ceil_div(ceil_div(c.C, kThreads / 64), 8);  // of one cell type
         const dim3 grid(c.any_walls ? 2 * blocks : blocks);
         if (c.grid_fast) {

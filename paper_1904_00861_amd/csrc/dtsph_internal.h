@@ -35,6 +35,7 @@ constexpr int kMaxBlock = 256;
 constexpr int kMaxRanges = 32;       // active tile ranges passed to the pair pass
 constexpr int kSegTiles = 256;       // tiles per residual segment (one finalize workgroup)
 constexpr int kSoloSegs = 4;          // segments that one finalize workgroup takes for a whole sim
+constexpr int kNbrCell = 64;          // neighbour-build "lanes" that mean one wavefront per cell
 constexpr int kMaxTileRows = 32;     // cell rows per strip of the staged neighbour kernel
 constexpr int kTailMaxSims = 256;    // sims of a context that may use tail launches
 constexpr int64_t kTailSpinDefault = 1LL << 22;  // polls of a tail barrier word before a wait gives up
@@ -117,8 +118,8 @@ struct Ctx {
     int cap = 0;             // neighbour-list capacity per particle
     int block = 256;
     int lpp = 1;             // lanes per particle in the pair pass
-    int g_nbr = 0, g_filter = 0;  // lanes per particle in the neighbour kernels (0: heuristic; g_nbr 64: a
-                                  // wavefront per cell)
+    int g_nbr = 0, g_filter = 0;  // lanes per particle in the neighbour kernels (0: heuristic; g_nbr kNbrCell:
+                                  // a wavefront per cell)
     // staged-tile neighbour kernel (2D contexts): 1 use it where it applies;
     // strip table {sim, cell type, first row, first column} for the current
     // subdivision, its capacity (the most strips of any subdivision), and the
