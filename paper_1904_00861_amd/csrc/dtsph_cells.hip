@@ -821,6 +821,17 @@ __device__ inline int sim_of_key(const SimDev *__restrict__ sims, int n_sims, in
     return a;
 }
 
+// Orders this wavefront's LDS accesses before it against those after it, where lanes
+// exchange entries without a barrier: LDS serves a wavefront's instructions in the
+// order in which it issues them, so only the compiler has to be kept from moving any
+// across. It adds no instruction.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kThreads)
 k_nbr_cell(NbrArgs<T> A, const SimDev *__restrict__ sims, const uint32_t *__restrict__ cstart,
@@ -909,11 +920,13 @@ k_nbr_cell(NbrArgs<T> A, const SimDev *__restrict__ sims, const uint32_t *__rest
         auto store = [&](auto list) __attribute__((always_inline)) {  // the waiting entries of a list
             constexpr int l = decltype(list)::value;
             const int most = most_of(pend[l]), mine = per_lane(pend[l]);
+            wave_lds_fence();  // other lanes' entries, written by test()
             for (int r0 = 0; r0 < most; r0 += 64 >> sh) {
                 const int q = r0 + (lane >> sh), r = done[l] + q;
                 if (pl < np && q < mine && r < cap[l])
                     out[l][(size_t)(unsigned)r * (unsigned)N + (ib + pl)] = lds[wave][l][pl][q];
             }
+            wave_lds_fence();  // read before test() writes the rows again
             done[l] += mine;
 #pragma unroll
             for (int p = 0; p < kCellBatch; ++p) pend[l][p] = 0;
