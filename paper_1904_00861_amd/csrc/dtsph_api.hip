@@ -1396,6 +1396,9 @@ static int create_impl(const dtsph_sim_desc *sims, const int64_t *n_fluid, const
                 c.g_filter = it->second[3];
                 c.nbr_tiles = c.strips ? it->second[5] : 0;
                 setup_keys(c, it->second[4]);
+                // tuned on a filled domain, but this one is mostly empty (the kind of a
+                // context does not tell): the automatic choice
+                if (c.g_nbr == kNbrCell && !cells_filled(c)) c.g_nbr = 0;
             }
         }
         const size_t max_tiles = (size_t)(Nf + n_sims + 8);

@@ -1274,7 +1274,7 @@ template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a,
 // lanes 88, 4 lanes 98; 300k: 2 lanes 181, 1 lane 190; 2.6M: 1 lane).
 int nbr_lanes_for(const Ctx &c)
 {
-    if ((c.max_dim == 3 || c.N < 20000) && c.C <= c.N) return kNbrCell;
+    if ((c.max_dim == 3 || c.N < 20000) && cells_filled(c)) return kNbrCell;
     return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 ? 2 : 1;
 }
 

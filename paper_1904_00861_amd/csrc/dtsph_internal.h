@@ -361,6 +361,9 @@ struct ApiError {
     ApiError(int s, std::string w) : status(s), what(std::move(w)) {}
 };
 
+// Do most cells hold particles? (One wavefront per cell pays only then.)
+inline bool cells_filled(const Ctx &c) { return c.C <= c.N; }
+
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Runs f(constants) for the sim of every lane, one sim of the wavefront at a time
