@@ -511,19 +511,36 @@ template <typename T> void alloc_state(Ctx &c)
 }
 
 // ---- timing -------------------------------------------------------------------
-hipEvent_t pool_event(Ctx &c, size_t k)
+// A pair of events that no pending launch holds (index of the first).
+int pool_events(Ctx &c)
 {
-    while (c.ev_pool.size() <= k) {
-        hipEvent_t e;
-        DTSPH_HIP_CHECK(hipEventCreate(&e));
-        c.ev_pool.push_back(e);
+    if (c.ev_free.empty()) {
+        for (int k = 0; k < 2; ++k) {
+            hipEvent_t e;
+            DTSPH_HIP_CHECK(hipEventCreate(&e));
+            c.ev_pool.push_back(e);
+        }
+        return (int)c.ev_pool.size() - 2;
     }
-    return c.ev_pool[k];
+    const int k = c.ev_free.back();
+    c.ev_free.pop_back();
+    return k;
 }
 
-void resolve_timers(Ctx &c)
+// Books the timed launches that came before the publishing launch with sequence
+// number `upto`, whose report has been read: their events are complete or about to
+// be. Later ones may belong to a group of iterations still in flight, which a wait
+// for them would drain.
+void resolve_timers(Ctx &c, int upto)
 {
+    size_t kept = 0;
     for (auto &pr : c.ev_pending) {
+        if (pr[3] - upto > 0) {
+            c.ev_pending[kept++] = pr;
+            continue;
+        }
+        c.ev_free.push_back(pr[0]);
+        if (pr[1] < 0) continue;
         float ms = 0.f;
         DTSPH_HIP_CHECK(hipEventSynchronize(c.ev_pool[pr[0] + 1]));
         DTSPH_HIP_CHECK(hipEventElapsedTime(&ms, c.ev_pool[pr[0]], c.ev_pool[pr[0] + 1]));
@@ -533,9 +550,11 @@ void resolve_timers(Ctx &c)
         else if (pr[1] == 2) { c.tstats.build_launches++; c.tstats.build_ms += ms; c.tstats.build_particles += c.N; }
         else { c.tstats.filter_launches++; c.tstats.filter_ms += ms; }
     }
-    c.ev_pending.clear();
-    c.ev_used = 0;
+    c.ev_pending.resize(kept);
 }
+
+// All of them (after a stream sync).
+void resolve_timers(Ctx &c) { resolve_timers(c, c.seq + 1); }
 
 // ---- flags / sync -------------------------------------------------------------
 // Build flags moved to mapped host memory by k_finalize / k_publish; the host
@@ -574,6 +593,7 @@ bool take_report(Ctx &c, int s, int want)
     h.iters = r.iters;
     h.reason = (int)(r.state & 255u);
     h.done = (int)((r.state >> 8) & 1u);
+    h.seq = (int)r.seq;
     h.moved = r.state >> 16;
     h.rp_mean = r.rp_mean;
     h.rv_mean = r.rv_mean;
@@ -826,6 +846,8 @@ template <typename T> void loop_prologue(Ctx &c, int fixed, LoopRun &L)
     launch_move_begin<T>(c);
     set_active_ranges(c, true);
     c.pass_times.clear();
+    for (auto &pr : c.ev_pending)
+        if (pr[1] == 0) pr[1] = -1;  // launched past the last loop's stop: not of this loop
     L.fixed = fixed;
     L.max_it = fixed;
     if (fixed == 0)
@@ -908,7 +930,7 @@ template <typename T> int loop_finish(Ctx &c, LoopRun &L, dtsph_iter_report *rep
 {
     for (;;) {
         wait_reports(c, L.window ? L.mark_seq[0] : c.seq);  // k_finalize wrote the mapped reports
-        if (c.timing) resolve_timers(c);
+        if (c.timing) resolve_timers(c, c.reps_host[c.n_sims - 1].seq);
         check_loop_flags(c);
         if (L.window) {
             L.known = L.mark_it[0];
@@ -1215,11 +1237,9 @@ int timer_begin(Ctx &c, int kind)
     if (!c.timing) return -1;
     if (c.in_segment && kind != 0) return -1;  // graph segments time pair passes only
     if (timer_skips(c, kind)) return -1;
-    size_t k = c.ev_used;
-    c.ev_used += 2;
-    DTSPH_HIP_CHECK(hipEventRecord(pool_event(c, k), c.stream));
-    pool_event(c, k + 1);
-    return (int)k;
+    const int k = pool_events(c);
+    DTSPH_HIP_CHECK(hipEventRecord(c.ev_pool[k], c.stream));
+    return k;
 }
 
 int timer_slot(Ctx &c, int kind)
@@ -1227,23 +1247,20 @@ int timer_slot(Ctx &c, int kind)
     if (!c.timing) return -1;
     if (c.in_segment && kind != 0) return -1;
     if (timer_skips(c, kind)) return -1;
-    size_t k = c.ev_used;
-    c.ev_used += 2;
-    pool_event(c, k + 1);
-    return (int)k;
+    return pool_events(c);
 }
 
 void timer_book(Ctx &c, int slot, int kind)
 {
     if (slot < 0) return;
-    c.ev_pending.push_back({slot, kind, kind == 0 ? c.pass_index : -1});
+    c.ev_pending.push_back({slot, kind, kind == 0 ? c.pass_index : -1, c.seq + 1});
 }
 
 void timer_end(Ctx &c, int slot, int kind)
 {
     if (slot < 0) return;
     DTSPH_HIP_CHECK(hipEventRecord(c.ev_pool[slot + 1], c.stream));
-    c.ev_pending.push_back({slot, kind, kind == 0 ? c.pass_index : -1});
+    c.ev_pending.push_back({slot, kind, kind == 0 ? c.pass_index : -1, c.seq + 1});
 }
 
 }  // namespace dtsph

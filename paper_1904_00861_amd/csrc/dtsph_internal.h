@@ -101,6 +101,7 @@ struct SimIter {
 // A report as the host has taken it.
 struct HostRep {
     int iters = 0, reason = 0, done = 0;
+    int seq = 0;
     uint32_t moved = 0;  // build flags named in it
     double rp_mean = 0, rv_mean = 0, rp_max = 0, rv_max = 0, disp = 0;
     long long pairs = 0;
@@ -273,8 +274,10 @@ struct Ctx {
     std::vector<std::pair<int, double>> pass_times;  // this loop's timed pair passes (index, ms)
     dtsph_timing tstats{};
     std::vector<hipEvent_t> ev_pool;
-    std::vector<std::array<int, 3>> ev_pending;  // (start event, kind, pass index)
-    size_t ev_used = 0;
+    // start event, kind (-1: drop it), pass index, and the sequence number of the
+    // first report published after the launch
+    std::vector<std::array<int, 4>> ev_pending;
+    std::vector<int> ev_free;             // start events of ev_pool not in ev_pending
 
     // HIP graphs of the step segment from the rate pass to the first chunk of
     // pseudo-iterations, keyed by everything that changes its launches
