@@ -1225,6 +1225,34 @@ __device__ __forceinline__ void finalize_few(const FinArgs &A, int4 sg)
     if (A.publish) publish_report(A, s, It);
 }
 
+// The two sides of the arrival count below, without the L2 write-back and L2
+// invalidation of an agent-scope release and acquire. This relies on gfx950, not on
+// the memory model: agent-scope (sc1) stores write through to memory and are counted
+// as done (vmcnt) once they are there, and agent-scope loads are served from there,
+// past the caches, so data that is only ever accessed with them needs the wait and
+// the order of the instructions, nothing else. The empty asm keeps the compiler from
+// moving any access across; other targets take the fences.
+__device__ inline void agent_stores_done()
+{
+#if defined(__gfx950__)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+#else
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+#endif
+}
+
+__device__ inline void agent_loads_fresh()
+{
+#if defined(__gfx950__)
+    asm volatile("" ::: "memory");
+#else
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#endif
+}
+
 // Segment g of the residual reduction; the last segment of a sim to arrive
 // closes the sim's iteration (stop test, report).
 __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
@@ -1271,21 +1299,21 @@ __device__ __forceinline__ void finalize_segment(const FinArgs &A, int g)
         }
         return;
     }
-    // The segment sums are written through with agent-scope stores and read back with
-    // agent-scope loads, and the arrival is counted once the stores have completed, so
-    // neither side needs an agent fence (an L2 write-back, an L2 invalidation): 518k
-    // particles with walls 8.7 -> 7.3 us, 160k 7.2 -> 6.5.
+    // The segment sums are written with agent-scope stores and read back with
+    // agent-scope loads, and the arrival is counted once the stores are done
+    // (agent_stores_done): 518k particles with walls 8.7 -> 7.3 us against agent
+    // fences on both sides, 160k 7.2 -> 6.5.
     if (threadIdx.x == 0) {
         double *p = (double *)(A.seg_p + g), *p2 = (double *)(A.seg_p2 + g);
         for (int k = 0; k < 4; ++k) __hip_atomic_store(p + k, red[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int k = 0; k < 2; ++k) __hip_atomic_store(p2 + k, red[4 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
+        agent_stores_done();
         last = __hip_atomic_fetch_add(&A.tickets[s], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                (uint32_t)(S.seg_count - 1);
     }
     __syncthreads();
     if (!last) return;
+    agent_loads_fresh();
     for (int k = 0; k < 6; ++k) red[k] = 0.0;
     const int seg_begin = S.seg_begin, seg_count = S.seg_count;
     for (int q = (int)threadIdx.x; q < seg_count; q += kFinThreads) {
