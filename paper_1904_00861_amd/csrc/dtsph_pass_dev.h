@@ -1075,7 +1075,7 @@ __device__ inline void publish_report(const FinArgs &A, int s, const SimIter &It
 // start (only the last one to arrive uses it), so these reads overlap the
 // partial sums instead of following the arrival ticket one by one.
 struct FinState {
-    int iters, fixed, conv_norm, stall_window, max_iter, steady, seg_begin, seg_count;
+    int iters, fixed, conv_norm, stall_window, max_iter, steady;
     double hp[kHist], hv[kHist];
     double dt, pscale, res_p, res_v, vref, tol, stall_rel;
 };
@@ -1093,8 +1093,6 @@ __device__ inline void load_fin_state(FinState &F, const SimIter &It, const SimD
     F.stall_window = S.stall_window;
     F.max_iter = S.max_iter;
     F.steady = S.steady;
-    F.seg_begin = S.seg_begin;
-    F.seg_count = S.seg_count;
     F.dt = S.dt;
     F.pscale = S.dt / (S.rho0 * S.c * S.c);
     F.res_p = S.res_p;
