@@ -1265,17 +1265,27 @@ template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a,
     }
 }
 
-// Neighbour kernel of a context that was not tuned: one wavefront per cell (kNbrCell) in 3D
-// (full builds of 262k particles, FP32: 414 us against 453 with 2 lanes per particle, the
-// best lane count; 104k, FP64: 204 against 292) and in 2D up to 20k particles (2.5k: 33
-// against 40 us with 8 lanes; 11.6k: 42 against 48; 25k: 50 both; 160k: 134 against 88 with 2
-// lanes), unless most cells are empty (the 0.5M-particle dam break has 1.5M: 881 against 228
-// us); otherwise the lanes per particle that measured best (25k: 8 lanes 50 us, 4 lanes 52; 160k: 2
-// lanes 88, 4 lanes 98; 300k: 2 lanes 181, 1 lane 190; 2.6M: 1 lane).
+// Lanes per particle of the neighbour kernel by the number of particles. Full builds in
+// us (sort and lists, FP32) with 8, 4, 2 and 1 lanes, 2D: 12k 41, 42, 45, 55; 40k 52, 47,
+// 49, 57; 65k 60, 50, 50, 56; 90k 69, 60, 55, 63; 130k 83, 70, 60, 65; 160k 95, 79, 72, 71;
+// 262k 140, 107, 86, 82; 360k 165, 128, 105, 105 (the 518k dam break and the 2.6M batch: 1
+// lane). 3D, a slab of ten particles: 36k 175, 181, 229, 329; 100k 323, 299, 318, 418; 256k
+// 706, 607, 557, 794; 1M 2560, 2089, 1846, 2290, so 3D keeps 2 lanes.
+int nbr_lanes_by_size(const Ctx &c)
+{
+    return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 || c.max_dim == 3 ? 2 : 1;
+}
+
+// Neighbour kernel of a context that was not tuned: one wavefront per cell (kNbrCell) in
+// 3D (full builds of 262k particles, FP32: 396 us against 461 with 2 lanes per particle, the
+// best lane count; 111k: 190 against 272; 14k: 66 against 103 with 8) and in 2D up to 20k
+// particles (12k: 36 against 41 with 8 lanes; 26k: 43 against 44; 40k: 51 against 47 with 4),
+// unless most cells are empty (a 262k blob in 27 times its volume: 1092 against 394 with 2
+// lanes; the 234k dam break: 360 against 87); otherwise lanes per particle by size.
 int nbr_lanes_for(const Ctx &c)
 {
     if ((c.max_dim == 3 || c.N < 20000) && cells_filled(c)) return kNbrCell;
-    return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 ? 2 : 1;
+    return nbr_lanes_by_size(c);
 }
 
 // lanes per particle in the neighbour kernels: the autotuner's choice, else
@@ -1303,7 +1313,7 @@ template <typename T> void launch_grouped(Ctx &c, const NbrArgs<T> &a, bool filt
         }
         if (!c.grid_general) return;
         general_only = true;
-        g = 8;
+        g = nbr_lanes_by_size(c);
     }
     if (g <= 0) {
         g = 1;

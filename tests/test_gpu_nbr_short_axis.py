@@ -1,0 +1,67 @@
+"""Contexts whose sims the kernel with one wavefront per cell leaves to the
+lanes-per-particle kernel (a periodic axis with too few cells): the automatic choice
+gives that kernel lanes for the context's size, not those of a small one. A large 3D
+slab, periodic and ten particles thick, builds its lists in the time of its best lane
+count; lists of a small one equal the brute-force oracle."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1904_00861_amd import dtsph as D
+from paper_1904_00861_amd import inputs as I
+
+from gpu_helpers import banner
+from test_gpu_nbr_cell_option import short_axis
+
+pytestmark = pytest.mark.gpu
+
+
+def _slab(n, thick):
+    """n x n x thick particles of a 3D lattice (jittered), periodic on every axis."""
+    prob = I.tgv3d(8)
+    dx, k = 1.0 / n, 8.0 / n
+    g = np.stack(np.meshgrid(*[(np.arange(m) + 0.5) * dx for m in (n, n, thick)], indexing="ij"), axis=-1)
+    hi = np.array([1.0, 1.0, thick * dx])
+    x = g.reshape(-1, 3) + np.random.default_rng(3).uniform(-0.05, 0.05, (n * n * thick, 3)) * dx
+    x = np.mod(x, hi)
+    prob.params.update(h=prob.params["h"] * k, dt=prob.params["dt"] * k, mass=prob.params["rho0"] * dx ** 3,
+                       lo=(0.0, 0.0, 0.0), hi=tuple(hi))
+    prob.x, prob.v, prob.v_prev, prob.p = x, np.zeros_like(x), np.zeros_like(x), np.zeros(len(x))
+    prob.n_fluid = len(x)
+    return prob
+
+
+@pytest.mark.parametrize("lanes", [0, 64])
+def test_lists_of_a_slab(lanes):
+    prob = _slab(16, 8)
+    banner(f"slab lists, neighbour-build lanes {lanes}")
+    assert short_axis(prob, 2)
+    ob, ib = O.neighbors(prob.params, prob.n_fluid, prob.n_wall, prob.x, "brute")
+    sim = D.Sim(prob, precision=D.FP32)
+    sim.set_option(D.OPT_NBR_LANES, lanes)
+    off, idx = sim.neighbor_list()
+    sim.close()
+    assert np.array_equal(off, ob) and np.array_equal(idx, ib)
+
+
+def test_large_slab_takes_lanes_for_its_size():
+    prob = _slab(160, 10)
+    banner(f"slab of {prob.n} particles: build time")
+    assert short_axis(prob, 2)
+    sim = D.Sim(prob, precision=D.FP32)
+    sim.set_option(D.OPT_TIMING, 1)
+    us = {}
+    for lanes in (2, 0, 8):
+        sim.set_option(D.OPT_NBR_LANES, lanes)
+        best = np.inf
+        for _ in range(4):
+            sim.set_option(D.OPT_RESET_TIMING, 0)
+            for _ in range(4):
+                sim.set_option(D.OPT_CELL_DIV, 2)  # the next use builds again
+                sim.build_cells()
+            t = sim.timing()
+            best = min(best, 1e3 * t["build_ms"] / t["build_launches"])
+        us[lanes] = best
+    sim.close()
+    print(f"[gpu-time] full build {us[0]:.1f} us automatic, {us[2]:.1f} us 2 lanes, {us[8]:.1f} us 8 lanes", flush=True)
+    assert us[0] < 0.5 * (us[2] + us[8])
