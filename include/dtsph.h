@@ -385,7 +385,7 @@ int dtsph_neighbor_list(dtsph_ctx *ctx, int32_t sim, int64_t *offsets, int32_t *
                                   lists and their order are the same. With 64,
                                   sims with a periodic axis of fewer than
                                   2 * cell subdivision + 3 cells take lanes
-                                  per particle by the context's size         */
+                                  per particle by their number of particles  */
 #define DTSPH_OPT_GRAPHS 10    /* 1: dtsph_step records the segment from the
                                   rate pass to the first chunk of pseudo-
                                   iterations as a HIP graph (one per launch

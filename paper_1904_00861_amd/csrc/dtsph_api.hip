@@ -339,8 +339,19 @@ void setup_keys(Ctx &c, int m)
     if (C > c.C_max) throw ApiError(DTSPH_EINVAL, "cell grid exceeds the key tables sized at creation");
     c.C = (int)C;
     c.cell_div = m;
-    c.grid_fast = c.grid_general = false;
-    for (const SimDev &S : c.sims_h) (S.general ? c.grid_general : c.grid_fast) = true;
+    c.grid_fast = false;
+    c.general[0] = c.general[1] = make_int2(0, 0);
+    for (const SimDev &S : c.sims_h) {
+        c.grid_fast = c.grid_fast || !S.general;
+        if (!S.general) continue;
+        const int2 own[2] = {make_int2(S.fluid_begin, S.fluid_begin + S.nf),
+                             make_int2(c.Nf + S.wall_begin, c.Nf + S.wall_begin + S.nw)};
+        for (int k = 0; k < 2; ++k) {  // (sims in slot order)
+            if (own[k].x == own[k].y) continue;
+            if (c.general[k].x == c.general[k].y) c.general[k] = own[k];
+            else c.general[k].y = own[k].y;
+        }
+    }
     setup_strips(c);
 }
 

@@ -691,15 +691,17 @@ __device__ __forceinline__ void scan_block(const NbrArgs<T> &A, const SimDev &S,
     ccw = cur.ctotal - ccf;
 }
 
-// GENERAL: the sims whose per-run shifts are not exact (SimDev::general); the
-// other launch takes the rest.
+// GENERAL: the sims whose per-run shifts are not exact (SimDev::general), in launches
+// over the slots `slots` that hold them (a batch of 15 sims of 62k particles and one of
+// 64, full build of 267 us: a launch over all slots with the batch's lanes added 17 us,
+// over its own slots with 8 lanes 8 us); the other launch takes the rest.
 template <typename T, int DIM, int G, bool GENERAL>
-__global__ void __launch_bounds__(kThreads) k_nbr(NbrArgs<T> A, const SimDev *__restrict__ sims)
+__global__ void __launch_bounds__(kThreads) k_nbr(NbrArgs<T> A, const SimDev *__restrict__ sims, int2 slots)
 {
     using Q = typename XR<DIM>::type;
     const Group<G> grp;
-    const int i = (blockIdx.x * blockDim.x + threadIdx.x) / G;
-    if (i >= A.N) return;  // whole groups leave together
+    const int i = slots.x + (int)((blockIdx.x * blockDim.x + threadIdx.x) / G);
+    if (i >= slots.y) return;  // whole groups leave together
     const bool fluid = i < A.Nf;
     const Q me = ((const Q *)A.xr)[i];
     for_each_sim(A.simid[i], sims, [&](const SimDev &S) {
@@ -1255,13 +1257,36 @@ __global__ void __launch_bounds__(kTileThreads) k_nbr_tile(NbrArgs<T> A, const i
 
 inline int grid_for(int n) { return n > 0 ? ceil_div(n, kThreads) : 1; }
 
-template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a, bool filter, bool general_only)
+// The kernels with lanes per particle: the filter, and the build's lists of the sims
+// without and with SimDev::general.
+enum class NbrJob { Filter, Fast, General };
+
+template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a, NbrJob job)
 {
-    const dim3 grid(grid_for((int)std::min<int64_t>((int64_t)a.N * G, INT32_MAX)));
-    if (filter) DTSPH_LAUNCH(c, (k_filter<T, DIM, G>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
-    else {
-        if (c.grid_fast && !general_only) DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, false>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
-        if (c.grid_general) DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, true>), grid, dim3(kThreads), 0, c.stream, a, c.sims);
+    auto grid = [](int n) { return dim3(grid_for((int)std::min<int64_t>((int64_t)n * G, INT32_MAX))); };
+    if (job == NbrJob::Filter) {
+        DTSPH_LAUNCH(c, (k_filter<T, DIM, G>), grid(a.N), dim3(kThreads), 0, c.stream, a, c.sims);
+    } else if (job == NbrJob::Fast) {
+        DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, false>), grid(a.N), dim3(kThreads), 0, c.stream, a, c.sims, make_int2(0, a.N));
+    } else {
+        for (const int2 &r : c.general)
+            if (r.x < r.y)
+                DTSPH_LAUNCH(c, (k_nbr<T, DIM, G, true>), grid(r.y - r.x), dim3(kThreads), 0, c.stream, a, c.sims, r);
+    }
+}
+
+template <typename T> void launch_lanes(Ctx &c, const NbrArgs<T> &a, NbrJob job, int g)
+{
+    if (c.max_dim == 2) {
+        if (g == 1) launch_g<T, 2, 1>(c, a, job);
+        else if (g == 2) launch_g<T, 2, 2>(c, a, job);
+        else if (g == 4) launch_g<T, 2, 4>(c, a, job);
+        else launch_g<T, 2, 8>(c, a, job);
+    } else {
+        if (g == 1) launch_g<T, 3, 1>(c, a, job);
+        else if (g == 2) launch_g<T, 3, 2>(c, a, job);
+        else if (g == 4) launch_g<T, 3, 4>(c, a, job);
+        else launch_g<T, 3, 8>(c, a, job);
     }
 }
 
@@ -1271,9 +1296,9 @@ template <typename T, int DIM, int G> void launch_g(Ctx &c, const NbrArgs<T> &a,
 // 262k 140, 107, 86, 82; 360k 165, 128, 105, 105 (the 518k dam break and the 2.6M batch: 1
 // lane). 3D, a slab of ten particles: 36k 175, 181, 229, 329; 100k 323, 299, 318, 418; 256k
 // 706, 607, 557, 794; 1M 2560, 2089, 1846, 2290, so 3D keeps 2 lanes.
-int nbr_lanes_by_size(const Ctx &c)
+int nbr_lanes_by_size(const Ctx &c, int n)
 {
-    return c.N < 40000 ? 8 : c.N < 131072 ? 4 : c.N < 524288 || c.max_dim == 3 ? 2 : 1;
+    return n < 40000 ? 8 : n < 131072 ? 4 : n < 524288 || c.max_dim == 3 ? 2 : 1;
 }
 
 // Neighbour kernel of a context that was not tuned: one wavefront per cell (kNbrCell) in
@@ -1285,51 +1310,45 @@ int nbr_lanes_by_size(const Ctx &c)
 int nbr_lanes_for(const Ctx &c)
 {
     if ((c.max_dim == 3 || c.N < 20000) && cells_filled(c)) return kNbrCell;
-    return nbr_lanes_by_size(c);
+    return nbr_lanes_by_size(c, c.N);
 }
 
-// lanes per particle in the neighbour kernels: the autotuner's choice, else
-// nbr_lanes_for; the filter enough threads for ~8 waves per SIMD
+// The neighbour kernels: the option's or the autotuner's choice, else the build's is
+// nbr_lanes_for and the filter takes enough threads for ~8 waves per SIMD. General sims
+// take lanes by the number of their slots where the choice is automatic or a wavefront
+// per cell.
 template <typename T> void launch_grouped(Ctx &c, const NbrArgs<T> &a, bool filter)
 {
-    bool general_only = false;
-    if (!filter && c.nbr_tiles && c.n_strips > 0) {
+    if (filter) {
+        int g = c.g_filter;
+        if (g <= 0) {
+            g = 1;
+            while (g < 8 && (int64_t)g * a.N < (int64_t)256 * 2048) g *= 2;
+        }
+        launch_lanes<T>(c, a, NbrJob::Filter, g);
+        return;
+    }
+    if (c.nbr_tiles && c.n_strips > 0) {
         const size_t lds = (size_t)c.tile_pmax * (sizeof(double2) + sizeof(int)) + (size_t)c.tile_offmax * sizeof(int);
         DTSPH_LAUNCH(c, k_nbr_tile<T>, dim3(c.n_strips), dim3(kTileThreads), lds, c.stream, a, c.strips, c.tile_pmax);
         return;
     }
-    int g = filter ? c.g_filter : c.g_nbr;
-    if (!filter && g <= 0) g = nbr_lanes_for(c);
-    if (g == kNbrCell) {
+    const int g = c.g_nbr > 0 ? c.g_nbr : nbr_lanes_for(c);
+    if (c.grid_fast && g == kNbrCell) {
         const int blocks = 8 * ceil_div(ceil_div(c.C, kThreads / 64), 8);  // of one cell type
         const dim3 grid(c.any_walls ? 2 * blocks : blocks);
-        if (c.grid_fast) {
-            if (c.max_dim == 2)
-                DTSPH_LAUNCH(c, (k_nbr_cell<T, 2>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
-                             (const double2 *)c.xr, c.n_sims, blocks);
-            else
-                DTSPH_LAUNCH(c, (k_nbr_cell<T, 3>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
-                             (const double4 *)c.xr, c.n_sims, blocks);
-        }
-        if (!c.grid_general) return;
-        general_only = true;
-        g = nbr_lanes_by_size(c);
+        if (c.max_dim == 2)
+            DTSPH_LAUNCH(c, (k_nbr_cell<T, 2>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
+                         (const double2 *)c.xr, c.n_sims, blocks);
+        else
+            DTSPH_LAUNCH(c, (k_nbr_cell<T, 3>), grid, dim3(kThreads), 0, c.stream, a, c.sims, c.cell_start,
+                         (const double4 *)c.xr, c.n_sims, blocks);
+    } else if (c.grid_fast) {
+        launch_lanes<T>(c, a, NbrJob::Fast, g);
     }
-    if (g <= 0) {
-        g = 1;
-        while (g < 8 && (int64_t)g * a.N < (int64_t)256 * 2048) g *= 2;
-    }
-    if (c.max_dim == 2) {
-        if (g == 1) launch_g<T, 2, 1>(c, a, filter, general_only);
-        else if (g == 2) launch_g<T, 2, 2>(c, a, filter, general_only);
-        else if (g == 4) launch_g<T, 2, 4>(c, a, filter, general_only);
-        else launch_g<T, 2, 8>(c, a, filter, general_only);
-    } else {
-        if (g == 1) launch_g<T, 3, 1>(c, a, filter, general_only);
-        else if (g == 2) launch_g<T, 3, 2>(c, a, filter, general_only);
-        else if (g == 4) launch_g<T, 3, 4>(c, a, filter, general_only);
-        else launch_g<T, 3, 8>(c, a, filter, general_only);
-    }
+    const int n = (c.general[0].y - c.general[0].x) + (c.general[1].y - c.general[1].x);
+    if (n > 0)
+        launch_lanes<T>(c, a, NbrJob::General, c.g_nbr > 0 && g != kNbrCell ? g : nbr_lanes_by_size(c, n));
 }
 
 }  // namespace

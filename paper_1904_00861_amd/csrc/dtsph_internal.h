@@ -115,7 +115,8 @@ struct Ctx {
     int C = 0;               // fluid cells of all sims; keys 0..2C-1
     int C_max = 0;           // C at the finest subdivision (sizes the key tables)
     int cell_div = 2;
-    bool grid_fast = true, grid_general = false;  // sims without / with SimDev::general
+    bool grid_fast = true;   // any sim without SimDev::general
+    int2 general[2] = {};    // slots from the first to past the last sim with it: fluid, walls (empty: x = y)
     int cap = 0;             // neighbour-list capacity per particle
     int block = 256;
     int lpp = 1;             // lanes per particle in the pair pass

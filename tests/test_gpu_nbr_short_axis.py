@@ -1,6 +1,6 @@
 """Contexts whose sims the kernel with one wavefront per cell leaves to the
 lanes-per-particle kernel (a periodic axis with too few cells): the automatic choice
-gives that kernel lanes for the context's size, not those of a small one. A large 3D
+gives that kernel lanes for the number of their particles, over their slots alone. A large 3D
 slab, periodic and ten particles thick, builds its lists in the time of its best lane
 count; lists of a small one equal the brute-force oracle."""
 import numpy as np
@@ -65,3 +65,35 @@ def test_large_slab_takes_lanes_for_its_size():
     sim.close()
     print(f"[gpu-time] full build {us[0]:.1f} us automatic, {us[2]:.1f} us 2 lanes, {us[8]:.1f} us 8 lanes", flush=True)
     assert us[0] < 0.5 * (us[2] + us[8])
+
+
+BATCHES = {  # short-axis members with and without walls: first, last, between others, all
+    "between": lambda: [I.tgv2d(20, seed=1), I.poiseuille(ny=12, nx=8), I.tgv2d(7, seed=2, jitter=0.2), I.cavity(9),
+                        I.poiseuille(ny=10, nx=7), I.tgv2d(24, seed=3)],
+    "first": lambda: [I.poiseuille(ny=12, nx=8), I.cavity(14), I.tgv2d(20, seed=1)],
+    "last": lambda: [I.cavity(14), I.tgv2d(20, seed=1), I.tgv2d(8, seed=4, jitter=0.2)],
+    "all": lambda: [I.tgv2d(7, seed=2, jitter=0.2), I.poiseuille(ny=12, nx=8), I.tgv2d(9, seed=5)],
+}
+
+
+@pytest.mark.parametrize("lanes", [0, 1, 4, 64])
+@pytest.mark.parametrize("batch", list(BATCHES))
+def test_lists_of_batches_with_short_axes(batch, lanes):
+    probs = BATCHES[batch]()
+    banner(f"lists of a batch, short axes {batch}, neighbour-build lanes {lanes}")
+    assert any(short_axis(p, 2) for p in probs) and (batch == "all") == all(short_axis(p, 2) for p in probs)
+    sim = D.Sim(probs, precision=D.FP32)
+    sim.set_option(D.OPT_NBR_TILES, 0)
+    sim.set_option(D.OPT_NBR_LANES, lanes)
+    try:
+        for s, prob in enumerate(probs):
+            ob, ib = O.neighbors(prob.params, prob.n_fluid, prob.n_wall, prob.x, "brute")
+            off, idx = sim.neighbor_list(s)
+            assert np.array_equal(off, ob) and np.array_equal(idx, ib), s
+        sim.set_option(D.OPT_CELL_DIV, 3)  # other sims have short axes then
+        for s, prob in enumerate(probs):
+            ob, ib = O.neighbors(prob.params, prob.n_fluid, prob.n_wall, prob.x, "brute")
+            off, idx = sim.neighbor_list(s)
+            assert np.array_equal(off, ob) and np.array_equal(idx, ib), s
+    finally:
+        sim.close()
