@@ -46,14 +46,15 @@ DTSPH_BOTH inline uint32_t report_check(const uint32_t w[16])
 DTSPH_BOTH inline uint32_t move_build_flags(int *flags, int *h_flags, uint32_t *moved)
 {
     uint32_t m = *moved;
-    for (int k = 0; k < F_COUNT; ++k) {
-        const int f = flags[k];
-        if (f) {
-            h_flags[k] = f;
+    int f[F_COUNT], any = 0;  // all loads at once: the report waits for them
+    for (int k = 0; k < F_COUNT; ++k) any |= f[k] = flags[k];
+    if (!any) return m;
+    for (int k = 0; k < F_COUNT; ++k)
+        if (f[k]) {
+            h_flags[k] = f[k];
             flags[k] = 0;
             m |= 1u << k;
         }
-    }
     *moved = m;
     return m;
 }
