@@ -787,7 +787,12 @@ void shift_decision(Ctx &c, bool use_cand)
     c.records_fresh = true;  // k_shift_apply rewrote the records
 }
 
-constexpr int kWindowLarge = 131072;  // particles from which launch_window goes by single iterations
+// Particles from which launch_window goes by single iterations instead of pairs. Steps of
+// single against pairs: 25.6k vortex 624 against 676 us, 36k dam break 1421 / 1461, 40k
+// vortex 638 / 673, 90k vortex 861 / 884, 91k cavity 2101 / 2183, 262k vortex 1248 / 1288,
+// 518k dam break 1429 / 1425; below: 22.5k steady cavity 699 / 690, 7k cavity 1979 / 1932,
+// 2.5k vortex 677 / 658 (some sizes there go the other way by 1 or 2%).
+constexpr int kWindowLarge = 24576;
 
 // A pseudo-time loop: set-up, chunks of iterations with a stop check after each,
 // and the bookkeeping at its end.
@@ -910,8 +915,8 @@ template <typename T> void launch_iterations(Ctx &c, LoopRun &L, int n)
 // The loop of a single sim: groups of iterations, two of them in flight, so that the
 // GPU works on one while the host reads the report of the other; up to the last
 // loop's count no further (a loop that needs as many stops there), past it always two.
-// A group takes longer than the host needs for a report and the next launches
-// (about 15 us), so single iterations from kWindowLarge particles on. Chunks of the last
+// A group takes about as long as the host needs for a report and the next launches
+// (15 us): two of the smallest iterations, one from kWindowLarge particles on. Chunks of the last
 // loop's length with a wait after each left the launches after the stop to run empty
 // (two kernels of 2-4 us each, a third of all iterations launched on the 518k dam break
 // and the 2.5k vortex) and the GPU idle for 10-25 us at each chunk's end.
