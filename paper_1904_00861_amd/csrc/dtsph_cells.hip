@@ -1295,10 +1295,12 @@ template <typename T> void launch_lanes(Ctx &c, const NbrArgs<T> &a, NbrJob job,
 // 49, 57; 65k 60, 50, 50, 56; 90k 69, 60, 55, 63; 130k 83, 70, 60, 65; 160k 95, 79, 72, 71;
 // 262k 140, 107, 86, 82; 360k 165, 128, 105, 105 (the 518k dam break and the 2.6M batch: 1
 // lane). 3D, a slab of ten particles: 36k 175, 181, 229, 329; 100k 323, 299, 318, 418; 256k
-// 706, 607, 557, 794; 1M 2560, 2089, 1846, 2290, so 3D keeps 2 lanes.
+// 706, 607, 557, 794; 1M 2560, 2089, 1846, 2290; sparse, 14k 80, 89, 111, 188; 47k 143, 116,
+// 135, 190; 111k 269, 220, 214, 246; 262k 581, 433, 394, 517.
 int nbr_lanes_by_size(const Ctx &c, int n)
 {
-    return n < 40000 ? 8 : n < 131072 ? 4 : n < 524288 || c.max_dim == 3 ? 2 : 1;
+    if (c.max_dim == 3) return n < 40000 ? 8 : n < 131072 ? 4 : 2;
+    return n < 40000 ? 8 : n < 65536 ? 4 : n < 524288 ? 2 : 1;
 }
 
 // Neighbour kernel of a context that was not tuned: one wavefront per cell (kNbrCell) in
