@@ -414,7 +414,7 @@ def main():
     if args.gpus != 1:
         print(f"bench.py runs on exactly one GPU; --gpus {args.gpus} is not supported "
               "(the batched workload shards whole simulations across GPUs without "
-              "communication, see DESIGN.md)", file=sys.stderr)
+              "communication)", file=sys.stderr)
         sys.exit(2)
     if args.summarize_counters:
         summarize_counters(args.summarize_counters)

@@ -3,7 +3,10 @@ for small 2D contexts): exact lists equal the brute-force oracle bit for bit whe
 wrong (cells with more particles than one batch of 8, lists longer than its LDS rows,
 candidates in many chunks of 64, walls, particles beyond the grid, periodic images in
 every axis, a batch that mixes it with sims whose axes are too short for it), and the
-order of the lists is that of the lanes-per-particle kernel: steps agree bit for bit."""
+order of the lists is that of the lanes-per-particle kernel: steps agree bit for bit.
+The choice is the library's own here: sims with too few cells on a periodic axis at a
+subdivision (the vortices at most) or more cells than particles (`beyond`) take the
+lanes-per-particle kernel; test_gpu_cell_order.py forces the kernel on sims it takes."""
 import numpy as np
 import pytest
 
