@@ -486,7 +486,8 @@ int dtsph_set_option(dtsph_ctx *ctx, int32_t option, int64_t value);
  * and keeps the fastest for this context; then the lanes per particle (1, 2,
  * 4, 8) of the candidate filter, timed the same way. The choice is cached per process by (dim, precision, walls,
  * artificial viscosity, fluid-count bucket) and applied to later contexts of
- * the same kind. out (host, may be NULL) receives every timing.             */
+ * the same kind (one wavefront per cell only to those with no more cells than
+ * particles, the others build with the automatic choice). out (host, may be NULL) receives every timing.             */
 typedef struct dtsph_tune_entry {
     int32_t lanes, block;
     double us; /* duration of one pass launch (best window's mean) */

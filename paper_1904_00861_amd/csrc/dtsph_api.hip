@@ -576,7 +576,7 @@ void check_host_flags(Ctx &c)
     const int over = c.flags_host[F_NBR_OVERFLOW], need = c.flags_host[F_NBR_NEEDED];
     const int cell = c.flags_host[F_CELL_OVERFLOW], outside = c.flags_host[F_OUTSIDE];
     const int skin = c.flags_host[F_SKIN];
-    if (over || need || cell || outside || skin) {  // (a word the device may be writing is left alone)
+    if (over || need || cell || outside || skin) {  // each of them is an error below
         for (int k = 0; k < F_COUNT; ++k) c.flags_host[k] = 0;
         mirror_push_flags(c);
     }
@@ -586,7 +586,7 @@ void check_host_flags(Ctx &c)
     if (outside)
         throw ApiError(DTSPH_EINVAL, "a position on a periodic axis lies outside [lo, hi); the state was not "
                                      "accepted (set it again)");
-    if (over)
+    if (over || need)
         throw ApiError(DTSPH_EOVERFLOW, "neighbour list capacity " + std::to_string(c.cap) + " exceeded; needs " +
                                             std::to_string(need) + " (set max_neighbors); particle state is undefined");
     if (cell)
